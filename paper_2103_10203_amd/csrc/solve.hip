@@ -480,50 +480,50 @@ void ev_end(SolveCtx& cx, int kind, hipEvent_t a) {
 
 // ------------------------------------------------------------------ launches
 template <int C, int NH, int V, int MODE, int MAT>
-void go_row_fast_v(SolveCtx& cx, Group& g, float* eps, float* sig, int rows) {
+void go_row_fast_v(SolveCtx& cx, Group& g, float* eps, float* sig, int rows, const Decide& dec) {
   if constexpr (V < RowVar<C, NH>::count) {
     using Cfg = RowCfg<C, NH, V>;
     dim3 gr((rows + Cfg::RB - 1) / Cfg::RB, (unsigned)g.rves.size());
     k_row_fast<C, NH, V, MODE, MAT><<<gr, row_threads<C, NH, V>(), row_lds_bytes<C, NH, V>(), cx.st>>>(
-        cx.d_plans, g.d_list, cx.d_st, cx.d_yl, cx.off, cx.mat, cx.d_jstate, eps, sig, cx.d_sigpart);
+        cx.d_plans, g.d_list, cx.d_st, cx.d_yl, cx.off, cx.mat, cx.d_jstate, eps, sig, cx.d_sigpart, dec);
   }
 }
 
 template <int C, int NH, int MODE, int MAT>
-void go_row_fast(SolveCtx& cx, Group& g, float* eps, float* sig, int rows) {
+void go_row_fast(SolveCtx& cx, Group& g, float* eps, float* sig, int rows, const Decide& dec) {
   static_assert(RowVar<C, NH>::count <= 11, "dispatch covers eleven variants");
   switch (g.rvar) {
-    case 0: go_row_fast_v<C, NH, 0, MODE, MAT>(cx, g, eps, sig, rows); break;
-    case 1: go_row_fast_v<C, NH, 1, MODE, MAT>(cx, g, eps, sig, rows); break;
-    case 2: go_row_fast_v<C, NH, 2, MODE, MAT>(cx, g, eps, sig, rows); break;
-    case 3: go_row_fast_v<C, NH, 3, MODE, MAT>(cx, g, eps, sig, rows); break;
-    case 4: go_row_fast_v<C, NH, 4, MODE, MAT>(cx, g, eps, sig, rows); break;
-    case 5: go_row_fast_v<C, NH, 5, MODE, MAT>(cx, g, eps, sig, rows); break;
-    case 6: go_row_fast_v<C, NH, 6, MODE, MAT>(cx, g, eps, sig, rows); break;
-    case 7: go_row_fast_v<C, NH, 7, MODE, MAT>(cx, g, eps, sig, rows); break;
-    case 8: go_row_fast_v<C, NH, 8, MODE, MAT>(cx, g, eps, sig, rows); break;
-    case 9: go_row_fast_v<C, NH, 9, MODE, MAT>(cx, g, eps, sig, rows); break;
-    default: go_row_fast_v<C, NH, 10, MODE, MAT>(cx, g, eps, sig, rows); break;
+    case 0: go_row_fast_v<C, NH, 0, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+    case 1: go_row_fast_v<C, NH, 1, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+    case 2: go_row_fast_v<C, NH, 2, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+    case 3: go_row_fast_v<C, NH, 3, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+    case 4: go_row_fast_v<C, NH, 4, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+    case 5: go_row_fast_v<C, NH, 5, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+    case 6: go_row_fast_v<C, NH, 6, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+    case 7: go_row_fast_v<C, NH, 7, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+    case 8: go_row_fast_v<C, NH, 8, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+    case 9: go_row_fast_v<C, NH, 9, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+    default: go_row_fast_v<C, NH, 10, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
   }
 }
 
 template <int C, int MODE, int MAT>
-void row_fast(SolveCtx& cx, Group& g, float* eps, float* sig) {
+void row_fast(SolveCtx& cx, Group& g, float* eps, float* sig, const Decide& dec = Decide{}) {
   const int nlen = C == 3 ? g.n1 : g.n2;
   const int rows = C == 3 ? g.n0 : g.n0 * g.n1;
   if constexpr (C == 3) {
     switch (nlen / 2) {
-      case 32: go_row_fast<3, 32, MODE, MAT>(cx, g, eps, sig, rows); break;
-      case 64: go_row_fast<3, 64, MODE, MAT>(cx, g, eps, sig, rows); break;
-      case 128: go_row_fast<3, 128, MODE, MAT>(cx, g, eps, sig, rows); break;
-      case 192: go_row_fast<3, 192, MODE, MAT>(cx, g, eps, sig, rows); break;
-      default: go_row_fast<3, 256, MODE, MAT>(cx, g, eps, sig, rows); break;
+      case 32: go_row_fast<3, 32, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+      case 64: go_row_fast<3, 64, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+      case 128: go_row_fast<3, 128, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+      case 192: go_row_fast<3, 192, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+      default: go_row_fast<3, 256, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
     }
   } else {
     switch (nlen / 2) {
-      case 32: go_row_fast<6, 32, MODE, MAT>(cx, g, eps, sig, rows); break;
-      case 64: go_row_fast<6, 64, MODE, MAT>(cx, g, eps, sig, rows); break;
-      default: go_row_fast<6, 128, MODE, MAT>(cx, g, eps, sig, rows); break;
+      case 32: go_row_fast<6, 32, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+      case 64: go_row_fast<6, 64, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
+      default: go_row_fast<6, 128, MODE, MAT>(cx, g, eps, sig, rows, dec); break;
     }
   }
 }
@@ -805,8 +805,24 @@ mor_status launch_row64(SolveCtx& cx, Group& g, dim3 gr, size_t shm, float* eps,
   }
 }
 
+// Whether a group's row kernel takes the stop decision of the iteration
+// before it (specialised kernels, grid schedule); else every iteration ends
+// with a k_converge launch.  The decision lengthens every row workgroup (it
+// waits for the sum), the launch costs 2.4-4.5 us, so the line lies where the
+// row workgroups no longer run all at once: in the row kernel against as a
+// launch, one 256^2 RVE (16 workgroups) 768 / 812 us per solve, one 512^2 J2
+// path (64) 27.3 / 29.2 ms, 128 RVEs of 256^2 (2048) 2.01 / 2.04 ms, 256 RVEs
+// (4096) 3.26 / 3.25 ms, eight of 128^3 (8192) 9.15 / 9.02 ms.
+constexpr int64_t kRowDecidesMax = 2048;
+bool row_decides(const SolveCtx& cx, const Group& g, int rows) {
+  return g.fast_row && !cx.persist && !cx.dft &&
+         (int64_t)((rows + g.rb - 1) / g.rb) * (int64_t)g.rves.size() <= kRowDecidesMax;
+}
+
+// One iteration of a group; first and last say whether it opens or ends a
+// chunk of iterations between two looks at the active count.
 template <int C, int MAT>
-mor_status launch_iter(SolveCtx& cx, Group& g) {
+mor_status launch_iter(SolveCtx& cx, Group& g, bool first, bool last) {
   const int nlen = C == 3 ? g.n1 : g.n2;
   const int rows = C == 3 ? g.n0 : g.n0 * g.n1;
   const int nh = nlen / 2;
@@ -814,6 +830,7 @@ mor_status launch_iter(SolveCtx& cx, Group& g) {
   dim3 gr((rows + g.rb - 1) / g.rb, (unsigned)g.rves.size());
   hipEvent_t a{};
   const bool pers = cx.persist && !cx.dft;
+  const Decide dec{cx.d_part, g.cb, cx.d_active};
   if (pers) {
     // queue of this iteration: the group's still-iterating RVEs
     k_active_list<<<1, 1024, 0, cx.st>>>(g.d_list, (int)g.rves.size(), cx.d_st, g.d_alist, cx.d_nact + g.gidx);
@@ -828,7 +845,7 @@ mor_status launch_iter(SolveCtx& cx, Group& g) {
   } else if (g.fast_row && pers)
     row_persist<C, MAT>(cx, g);
   else if (g.fast_row)
-    row_fast<C, MODE_ITER, MAT>(cx, g, nullptr, nullptr);
+    row_fast<C, MODE_ITER, MAT>(cx, g, nullptr, nullptr, !first && row_decides(cx, g, rows) ? dec : Decide{});
   else
     k_row<C, MODE_ITER, MAT><<<gr, 256, shr, cx.st>>>(cx.d_plans, g.d_list, cx.d_st, cx.d_yl, cx.off, cx.mat,
                                                       cx.d_jstate, nullptr, nullptr, nullptr, g.rb);
@@ -862,10 +879,12 @@ mor_status launch_iter(SolveCtx& cx, Group& g) {
     ev_end(cx, PK_MIDI, a);
   }
   // the stop decision comes last: every stage of this iteration has run
-  const int nrv = (int)g.rves.size();
-  k_converge<<<(nrv + kConvergeRvesPerBlock - 1) / kConvergeRvesPerBlock, 256, 0, cx.st>>>(
-      cx.d_plans, g.d_list, nrv, cx.d_st, cx.d_part, cx.off, g.cb, cx.d_active);
-  MOR_LAUNCH_CHECK("converge");
+  if (last || !row_decides(cx, g, rows)) {
+    const int nrv = (int)g.rves.size();
+    k_converge<<<(nrv + kConvergeRvesPerBlock - 1) / kConvergeRvesPerBlock, 256, 0, cx.st>>>(
+        cx.d_plans, g.d_list, nrv, cx.d_st, cx.off, dec);
+    MOR_LAUNCH_CHECK("converge");
+  }
   return MOR_OK;
 }
 
@@ -905,9 +924,16 @@ mor_status launch_final(SolveCtx& cx, Group& g, float* eps, float* sig) {
 mor_status do_init(SolveCtx& cx, Group& g, const cpx<float>* warm) {
   return cx.C == 3 ? launch_init<3>(cx, g, warm) : launch_init<6>(cx, g, warm);
 }
-mor_status do_iter(SolveCtx& cx, Group& g) {
-  if (cx.C == 3) return cx.j2 ? launch_iter<3, MAT_J2>(cx, g) : launch_iter<3, MAT_HOOKE>(cx, g);
-  return cx.j2 ? launch_iter<6, MAT_J2>(cx, g) : launch_iter<6, MAT_HOOKE>(cx, g);
+mor_status do_iter(SolveCtx& cx, Group& g, bool first, bool last) {
+  if (cx.C == 3)
+    return cx.j2 ? launch_iter<3, MAT_J2>(cx, g, first, last) : launch_iter<3, MAT_HOOKE>(cx, g, first, last);
+  return cx.j2 ? launch_iter<6, MAT_J2>(cx, g, first, last) : launch_iter<6, MAT_HOOKE>(cx, g, first, last);
+}
+// The iterations of a chunk of one group.
+mor_status do_chunk(SolveCtx& cx, Group& g, int check) {
+  mor_status s = MOR_OK;
+  for (int k = 0; k < check && s == MOR_OK; ++k) s = do_iter(cx, g, k == 0, k == check - 1);
+  return s;
 }
 mor_status do_final(SolveCtx& cx, Group& g, float* eps, float* sig) {
   if (cx.C == 3) return cx.j2 ? launch_final<3, MAT_J2>(cx, g, eps, sig) : launch_final<3, MAT_HOOKE>(cx, g, eps, sig);
@@ -1226,8 +1252,7 @@ struct GraphChunk {
     hipError_t e = hipStreamBeginCapture(cx.st, hipStreamCaptureModeThreadLocal);
     if (e == hipSuccess) {
       for (auto& g : cx.groups)
-        for (int k = 0; k < check && s == MOR_OK; ++k)
-          if ((s = do_iter(cx, g)) != MOR_OK) break;
+        if ((s = do_chunk(cx, g, check)) != MOR_OK) break;
       hipError_t e2 = hipStreamEndCapture(cx.st, &graph);
       if (e2 != hipSuccess && s == MOR_OK) e = e2;
     }
@@ -1273,8 +1298,7 @@ mor_status run(SolveCtx& cx, const cpx<float>* warm, const mor_solve_opts* opts,
     } else {
       // sub-batch outermost: its lines stay cached across its iterations
       for (auto& g : cx.groups)
-        for (int k = 0; k < check; ++k)
-          if ((s = do_iter(cx, g)) != MOR_OK) return s;
+        if ((s = do_chunk(cx, g, check)) != MOR_OK) return s;
     }
     done += check;
     unsigned int* hact = cx.noalloc ? &cx.h_active_local : cx.ws->h_active;

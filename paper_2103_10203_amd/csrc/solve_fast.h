@@ -156,7 +156,8 @@ template <int C, int NH, int V, int MODE, int MAT>
 __device__ __forceinline__ void row_tile(const PlanDev* __restrict__ plans, const int b, const int tile,
                                          RveState* __restrict__ st, cpx<float>* __restrict__ Yl, const Offs& off,
                                          const MatDev& mat, float* __restrict__ jstate, float* __restrict__ out_eps,
-                                         float* __restrict__ out_sig, double* __restrict__ sig_part, const int tid) {
+                                         float* __restrict__ out_sig, double* __restrict__ sig_part,
+                                         const Decide& dec, const int tid) {
   using Cfg = RowCfg<C, NH, V>;
   constexpr int RL = Cfg::RL, RB = Cfg::RB;
   constexpr int PS = PadOf<Cfg>::v;
@@ -185,6 +186,24 @@ __device__ __forceinline__ void row_tile(const PlanDev* __restrict__ plans, cons
   cpx<float>* T = reinterpret_cast<cpx<float>*>(smem_raw);
   cpx<float>* buf = T + row_tw_len<NH>();  // RB sequences, one component
   const int nlast = P.nlast;
+  // Stop decision of the previous iteration, taken by the first wavefront of
+  // every tile (same order of the sum, so same result, in each) and recorded
+  // by tile 0; tiles that start after that see active = 0 above, which is the
+  // same decision.  The loads are issued here and summed while the first
+  // gather is in flight: nothing is stored before the check.  It saves the
+  // launch of k_converge (2.4-4.5 us of the 21-26 us an iteration of one
+  // 256^2 or 512^2 RVE took).
+  __shared__ int stopped;
+  const bool decide = MODE == MODE_ITER && dec.part != nullptr;
+  const double* dpart = nullptr;
+  int dnum = 0;
+  double dp0 = 0.0, dp1 = 0.0;
+  if (decide && tid < 64) {
+    dpart = dec.part + off.part[b];
+    dnum = (P.ncol + dec.cb - 1) / dec.cb;
+    if (tid < dnum) dp0 = dpart[tid];
+    if (tid + 64 < dnum) dp1 = dpart[tid + 64];
+  }
   for (int t = tid; t < L; t += NT) T[pad16(t)] = P.rtw[t];
   for (int t = tid; t <= NH; t += NT) kofs[t] = kOutOfRange;
   for (int t = tid; t < nlast; t += NT) lk[t] = P.last_k[t];
@@ -234,6 +253,15 @@ __device__ __forceinline__ void row_tile(const PlanDev* __restrict__ plans, cons
 #pragma unroll
   for (int j = 0; j < RL; ++j) rtw[j] = fftr::twid<+1, 2>(T, j * i * (NH / (TR * RL)));
   gather(0);
+  if (decide && tid < 64) {
+    const double sum = part_sum(dpart, dnum, tid, dp0, dp1);
+    if (tid == 0) {
+      double res = 0.0;
+      const int end = stop_rule(st[b], sum, &res);
+      stopped = end >= 0;
+      if (tile == 0) stop_rve(st[b], end, res, dec.active);
+    }
+  }
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     // pack into the length-NH sequence
@@ -254,6 +282,7 @@ __device__ __forceinline__ void row_tile(const PlanDev* __restrict__ plans, cons
     }
     if (c + 1 < C) gather(c + 1);
     __syncthreads();
+    if (c == 0 && decide && stopped) return;
     fftr::lds_passes<NH, +1, 1, RB, SS, NT, 2, PS, true>(buf, T, tid, typename Cfg::RA{});
     // register pass: last inverse stage (radix RL, span TR)
     {
@@ -401,9 +430,9 @@ __global__ __launch_bounds__((row_threads<C, NH, V>())) __attribute__((amdgpu_wa
     MAT == MAT_HOOKE ? WavesOf<RowCfg<C, NH, V>>::v : 1))) void k_row_fast(
     const PlanDev* __restrict__ plans, const int* __restrict__ rve_list, RveState* __restrict__ st,
     cpx<float>* __restrict__ Yl, Offs off, MatDev mat, float* __restrict__ jstate, float* __restrict__ out_eps,
-    float* __restrict__ out_sig, double* __restrict__ sig_part) {
+    float* __restrict__ out_sig, double* __restrict__ sig_part, Decide dec) {
   row_tile<C, NH, V, MODE, MAT>(plans, rve_list[blockIdx.y], blockIdx.x, st, Yl, off, mat, jstate, out_eps, out_sig,
-                                sig_part, threadIdx.x);
+                                sig_part, dec, threadIdx.x);
 }
 
 // Persistent schedule: a fixed grid walks the (active RVE, tile) items of
@@ -419,7 +448,7 @@ __global__ __launch_bounds__((row_threads<C, NH, V>())) void k_row_persist(
     const int b = __builtin_amdgcn_readfirstlane(alist[q / ntiles]);
     const int tile = __builtin_amdgcn_readfirstlane(q % ntiles);
     row_tile<C, NH, V, MODE_ITER, MAT>(plans, b, tile, st, Yl, off, mat, jstate, nullptr, nullptr, nullptr,
-                                       opaque_tid());
+                                       Decide{}, opaque_tid());
     __syncthreads();  // the next item reuses the LDS buffers
   }
 }
@@ -672,7 +701,10 @@ __device__ __forceinline__ void col_tile(const PlanDev* __restrict__ plans, cons
   if (MODE == MODE_ITER) {
     __shared__ double red[16];
     const double tot = block_sum_d(dsum, red);
-    if (tid == 0) part[off.part[b] + tile] = tot;
+    if (tid == 0) {
+      part[off.part[b] + tile] = tot;
+      if (tile == 0) st[b].iters += 1;  // read by the stop decision, after this launch
+    }
   }
 }
 

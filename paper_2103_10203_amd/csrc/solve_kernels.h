@@ -516,7 +516,10 @@ __global__ __launch_bounds__(256) void k_col(const PlanDev* __restrict__ plans, 
   if (MODE == MODE_ITER) {
     __shared__ double red[16];
     const double tot = block_sum_d(dsum, red);
-    if (threadIdx.x == 0) part[off.part[b] + blockIdx.x] = tot;
+    if (threadIdx.x == 0) {
+      part[off.part[b] + blockIdx.x] = tot;
+      if (blockIdx.x == 0) st[b].iters += 1;  // read by the stop decision, after this launch
+    }
   }
 }
 
@@ -613,46 +616,86 @@ __global__ __launch_bounds__(256) void k_warm_check(const PlanDev* __restrict__ 
   if (threadIdx.x == 0) st[b].warm_ok = bad ? 0 : 1;
 }
 
-// Convergence decision after a column pass (one wavefront per RVE, 4 per
-// workgroup): FP64 sum of the column blocks' squared coefficient changes in a
-// fixed order (lane-strided partial sums, then a butterfly over the lanes),
-// Parseval residual r = sqrt(sum) / (N ||eps_bar||_F), and the stop rules.
+// ------------------------------------------------------------------ stop decision
+// A double moved between lanes by a DPP control (no LDS trip as in a shuffle).
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// FP64 sum of an RVE's partial sums by one wavefront, in a fixed order
+// (lane-strided partial sums, then a tree over the lanes: neighbours, pairs,
+// quads and halves of 16 by DPP, rows of 16 by shuffles): every wavefront
+// that computes it gets the same value, in every lane.  p0 and p1 are the
+// lane's first two partials (0 past the end), loaded by the caller.
+__device__ __forceinline__ double part_sum(const double* __restrict__ p, int n, int lane, double p0, double p1) {
+  double sum = p0 + p1;
+  for (int q = lane + 128; q < n; q += 64) sum += p[q];
+  sum += dpp_d<0xB1>(sum);   // quad_perm 1,0,3,2
+  sum += dpp_d<0x4E>(sum);   // quad_perm 2,3,0,1
+  sum += dpp_d<0x141>(sum);  // row_half_mirror
+  sum += dpp_d<0x140>(sum);  // row_mirror
+  sum += __shfl_xor(sum, 16, 64);
+  sum += __shfl_xor(sum, 32, 64);
+  return sum;
+}
+
+// Parseval residual r = sqrt(sum) / (N ||eps_bar||_F) of the iteration the
+// RVE has just done, and the stop rules.  Returns the status the RVE ends
+// with, or -1 to go on.  Far from the tolerance the squares decide, without
+// the root and the quotient (every row tile waits for this).
+__device__ __forceinline__ int stop_rule(const RveState& S, double sum, double* r_out) {
+  const double t = S.tol * S.denom, t2 = t * t;
+  if (sum > t2 * (1.0 + 1e-12) && sum < 1e300 && S.iters < S.max_iter) return -1;
+  const double r = sqrt(sum) / S.denom;
+  *r_out = r;
+  if (!(r == r) || isinf(r)) return MOR_E_NONFINITE;
+  if (r < S.tol) return MOR_OK;
+  if (S.iters >= S.max_iter) return MOR_E_NOT_CONVERGED;
+  return -1;
+}
+
+// Ends an RVE (one thread per RVE).
+__device__ __forceinline__ void stop_rve(RveState& S, int status, double r, unsigned int* __restrict__ active_count) {
+  if (status < 0) return;
+  S.resid = r;
+  S.status = status;
+  S.active = 0;
+  atomicSub(active_count, 1u);
+}
+
+// What a row kernel needs to take the stop decision of the iteration before
+// it: the column blocks' partial sums, the columns per block, the counter of
+// iterating RVEs.  part = nullptr: the decision has been taken.
+struct Decide {
+  const double* part;
+  int cb;
+  unsigned int* active;
+};
+
+// The stop decision as a launch of its own (one wavefront per RVE, 4 per
+// workgroup): after the last iteration of a chunk, so that the host sees the
+// count, and after every iteration of the kernels that do not take it
+// themselves.
 constexpr int kConvergeRvesPerBlock = 4;
 __global__ __launch_bounds__(256) void k_converge(const PlanDev* __restrict__ plans,
                                                   const int* __restrict__ rve_list, int nrve,
-                                                  RveState* __restrict__ st, const double* __restrict__ part,
-                                                  Offs off, int cb, unsigned int* __restrict__ active_count) {
+                                                  RveState* __restrict__ st, Offs off, Decide dec) {
   const int i = blockIdx.x * kConvergeRvesPerBlock + (int)(threadIdx.x >> 6);
   const int lane = (int)(threadIdx.x & 63);
   if (i >= nrve) return;  // uniform over the wavefront
   const int b = rve_list[i];
   RveState& S = st[b];
   if (!S.active) return;
-  const int nblk = (plans[S.plan].ncol + cb - 1) / cb;
-  double sum = 0.0;
-  for (int q = lane; q < nblk; q += 64) sum += part[off.part[b] + q];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+  const double* p = dec.part + off.part[b];
+  const int n = (plans[S.plan].ncol + dec.cb - 1) / dec.cb;
+  const double sum = part_sum(p, n, lane, lane < n ? p[lane] : 0.0, lane + 64 < n ? p[lane + 64] : 0.0);
   if (lane != 0) return;
-  const double r = sqrt(sum) / S.denom;
-  const int it = S.iters + 1;
-  S.iters = it;
-  S.resid = r;
-  int done = 0;
-  if (!(r == r) || isinf(r)) {
-    S.status = MOR_E_NONFINITE;
-    done = 1;
-  } else if (r < S.tol) {
-    S.status = MOR_OK;
-    done = 1;
-  } else if (it >= S.max_iter) {
-    S.status = MOR_E_NOT_CONVERGED;
-    done = 1;
-  }
-  if (done) {
-    S.active = 0;
-    atomicSub(active_count, 1u);
-  }
+  double r = 0.0;
+  const int end = stop_rule(S, sum, &r);
+  stop_rve(S, end, r, dec.active);
 }
 
 // Per-RVE grid mean of the stress: FP64 sum of the block partials divided by
