@@ -133,7 +133,7 @@ int cols_per_block(int C, int n0, int es = 8) {
 struct Group {
   int ndim, n0, n1, n2;
   std::vector<int> rves;
-  int ncol_max = 0, nlast_max = 0;
+  int ncol_max = 0, nlast_max = 0, ncoef_max = 0;
   int rb = 1, cb = 1, xb = 1;
   int rvar = 0;  // row-kernel variant
   int cvar = 0;  // column-kernel variant
@@ -1050,6 +1050,7 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
     g.rves.push_back((int)b);
     g.ncol_max = std::max(g.ncol_max, p->dev.ncol);
     g.nlast_max = std::max(g.nlast_max, p->dev.nlast);
+    g.ncoef_max = std::max(g.ncoef_max, p->dev.ncoef);
   }
   // offsets
   std::vector<int64_t> offs(5 * B);
@@ -1273,8 +1274,11 @@ mor_status run(SolveCtx& cx, const cpx<float>* warm, const mor_solve_opts* opts,
   if (warm) {
     // an RVE whose warm coefficients hold a NaN/Inf starts cold instead
     for (auto& g : cx.groups) {
-      k_warm_check<<<(unsigned)g.rves.size(), 256, 0, cx.st>>>(cx.d_plans, g.d_list, (int)g.rves.size(), cx.d_st,
-                                                               warm, cx.off, cx.C);
+      const dim3 gw((unsigned)((g.ncoef_max + kWarmCheckSlice - 1) / kWarmCheckSlice), (unsigned)g.rves.size());
+      if (cx.C == 3)
+        k_warm_check<3><<<gw, 256, 0, cx.st>>>(cx.d_plans, g.d_list, cx.d_st, warm, cx.off);
+      else
+        k_warm_check<6><<<gw, 256, 0, cx.st>>>(cx.d_plans, g.d_list, cx.d_st, warm, cx.off);
       MOR_LAUNCH_CHECK("warm_check");
     }
   }

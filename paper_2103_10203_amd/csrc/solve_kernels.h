@@ -591,29 +591,35 @@ __global__ __launch_bounds__(256) void k_mid(const PlanDev* __restrict__ plans, 
   }
 }
 
-// Warm-start guard: one workgroup per RVE scans its warm coefficients (the
-// zero-frequency and dropped entries are not used and are skipped); a NaN or
-// Inf anywhere makes the RVE start cold instead, so the iteration still runs
-// from a finite compatible field.
+// Warm-start guard: workgroup (slice, RVE) scans a slice of the RVE's warm
+// coefficients (the zero-frequency and dropped entries are not used and are
+// skipped); a NaN or Inf anywhere makes the RVE start cold instead, so the
+// iteration still runs from a finite compatible field.  Bound by the read of
+// the coefficients: sliced over the device, because one workgroup per RVE
+// took 200 us for the full set of 16 RVEs of 256^2 (2.4 MB of coefficients
+// each) and 41 us for one RVE of 512^2 at 5 %.  The states start with
+// warm_ok = 1 and a bad slice only ever stores 0, so the slices need no order.
+constexpr int kWarmCheckSlice = 1024;  // coefficients of one component per workgroup
+template <int C>
 __global__ __launch_bounds__(256) void k_warm_check(const PlanDev* __restrict__ plans,
-                                                    const int* __restrict__ rve_list, int nrve,
+                                                    const int* __restrict__ rve_list,
                                                     RveState* __restrict__ st, const cpx<float>* __restrict__ warm,
-                                                    Offs off, int C) {
-  const int i = blockIdx.x;
-  if (i >= nrve) return;
-  const int b = rve_list[i];
+                                                    Offs off) {
+  const int b = rve_list[blockIdx.y];
   const PlanDev& P = plans[st[b].plan];
   const int ncoef = P.ncoef;
   const cpx<float>* w = warm + off.coef[b];
+  const int e1 = min(ncoef, ((int)blockIdx.x + 1) * kWarmCheckSlice);
   int bad = 0;
-  for (int t = threadIdx.x; t < C * ncoef; t += blockDim.x) {
-    const int e = t % ncoef;
+  for (int e = blockIdx.x * kWarmCheckSlice + threadIdx.x; e < e1; e += blockDim.x) {
     if (P.coef_flag[e] & (COEF_ZERO | COEF_DEAD)) continue;
-    const cpx<float> v = w[t];
-    bad |= (isfinite(v.x) && isfinite(v.y)) ? 0 : 1;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const cpx<float> v = w[(int64_t)c * ncoef + e];
+      bad |= (isfinite(v.x) && isfinite(v.y)) ? 0 : 1;
+    }
   }
-  bad = __syncthreads_or(bad);
-  if (threadIdx.x == 0) st[b].warm_ok = bad ? 0 : 1;
+  if (__any(bad) && (threadIdx.x & 63) == 0) st[b].warm_ok = 0;
 }
 
 // ------------------------------------------------------------------ stop decision
