@@ -18,7 +18,8 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libmor.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["plan.hip", "solve.hip", "mlp.hip", "error.hip"]
+SOURCES = ["solve.hip", "cp_row_2d.hip", "cp_row_3d.hip", "cp_row_f64.hip", "cp_col.hip", "plan.hip", "mlp.hip",
+           "error.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
@@ -51,7 +52,7 @@ def build(verbose: bool = False, extra_flags=None) -> str:
             print(r.stderr, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
         objs = list(ex.map(compile_one, SOURCES))
     tmp = OUT + ".tmp"
     cmd = [hipcc, "-shared", "--offload-arch=gfx950", "-fPIC", *objs, "-o", tmp]

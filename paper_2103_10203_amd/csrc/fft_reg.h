@@ -16,31 +16,31 @@
 
 namespace fftr {
 
-template <int SIGN>
-__device__ __forceinline__ cpx<float> mul_i(cpx<float> a) {
-  return SIGN > 0 ? cpx<float>{-a.y, a.x} : cpx<float>{a.y, -a.x};
+template <int SIGN, typename T>
+__device__ __forceinline__ cpx<T> mul_i(cpx<T> a) {
+  return SIGN > 0 ? cpx<T>{-a.y, a.x} : cpx<T>{a.y, -a.x};
 }
 
 // cos and sin of 2 pi k / 16 for k = 0..8
-__host__ __device__ constexpr float c16(int k) {
-  return k == 0 ? 1.0f : k == 1 ? 0.92387953251128674f : k == 2 ? 0.70710678118654752f
-       : k == 3 ? 0.38268343236508977f : k == 4 ? 0.0f : k == 5 ? -0.38268343236508977f
-       : k == 6 ? -0.70710678118654752f : k == 7 ? -0.92387953251128674f : -1.0f;
+__host__ __device__ constexpr double c16(int k) {
+  return k == 0 ? 1.0 : k == 1 ? 0.92387953251128674 : k == 2 ? 0.70710678118654752
+       : k == 3 ? 0.38268343236508977 : k == 4 ? 0.0 : k == 5 ? -0.38268343236508977
+       : k == 6 ? -0.70710678118654752 : k == 7 ? -0.92387953251128674 : -1.0;
 }
-__host__ __device__ constexpr float s16(int k) {
-  return k == 0 ? 0.0f : k == 1 ? 0.38268343236508977f : k == 2 ? 0.70710678118654752f
-       : k == 3 ? 0.92387953251128674f : k == 4 ? 1.0f : k == 5 ? 0.92387953251128674f
-       : k == 6 ? 0.70710678118654752f : k == 7 ? 0.38268343236508977f : 0.0f;
+__host__ __device__ constexpr double s16(int k) {
+  return k == 0 ? 0.0 : k == 1 ? 0.38268343236508977 : k == 2 ? 0.70710678118654752
+       : k == 3 ? 0.92387953251128674 : k == 4 ? 1.0 : k == 5 ? 0.92387953251128674
+       : k == 6 ? 0.70710678118654752 : k == 7 ? 0.38268343236508977 : 0.0;
 }
 
-template <int SIGN, int K>
-__device__ __forceinline__ cpx<float> rot16(cpx<float> a) {
+template <int SIGN, int K, typename T>
+__device__ __forceinline__ cpx<T> rot16(cpx<T> a) {
   // a * exp(SIGN 2 pi i K / 16), K in [0, 8)
   if constexpr (K == 0) return a;
   else if constexpr (K == 4) return mul_i<SIGN>(a);
   else {
-    constexpr float c = c16(K);
-    constexpr float s = SIGN * s16(K);
+    constexpr T c = (T)c16(K);
+    constexpr T s = (T)(SIGN * s16(K));
     return {a.x * c - a.y * s, a.x * s + a.y * c};
   }
 }
@@ -50,8 +50,9 @@ struct Dft;
 
 template <int SIGN>
 struct Dft<2, SIGN> {
-  __device__ __forceinline__ static void run(cpx<float>* v) {
-    cpx<float> a = v[0], b = v[1];
+  template <typename T>
+  __device__ __forceinline__ static void run(cpx<T>* v) {
+    cpx<T> a = v[0], b = v[1];
     v[0] = cadd(a, b);
     v[1] = csub(a, b);
   }
@@ -59,12 +60,13 @@ struct Dft<2, SIGN> {
 
 template <int SIGN>
 struct Dft<3, SIGN> {
-  __device__ __forceinline__ static void run(cpx<float>* v) {
-    const float h = 0.86602540378443864676f;
-    cpx<float> u0 = v[0], u1 = v[1], u2 = v[2];
-    cpx<float> sm = cadd(u1, u2);
-    cpx<float> df = cscale(mul_i<SIGN>(csub(u1, u2)), h);
-    cpx<float> base = {u0.x - 0.5f * sm.x, u0.y - 0.5f * sm.y};
+  template <typename T>
+  __device__ __forceinline__ static void run(cpx<T>* v) {
+    const T h = (T)0.86602540378443864676;
+    cpx<T> u0 = v[0], u1 = v[1], u2 = v[2];
+    cpx<T> sm = cadd(u1, u2);
+    cpx<T> df = cscale(mul_i<SIGN>(csub(u1, u2)), h);
+    cpx<T> base = {u0.x - T(0.5) * sm.x, u0.y - T(0.5) * sm.y};
     v[0] = cadd(u0, sm);
     v[1] = cadd(base, df);
     v[2] = csub(base, df);
@@ -73,9 +75,10 @@ struct Dft<3, SIGN> {
 
 template <int SIGN>
 struct Dft<4, SIGN> {
-  __device__ __forceinline__ static void run(cpx<float>* v) {
-    cpx<float> s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
-    cpx<float> s13 = cadd(v[1], v[3]), d13 = mul_i<SIGN>(csub(v[1], v[3]));
+  template <typename T>
+  __device__ __forceinline__ static void run(cpx<T>* v) {
+    cpx<T> s02 = cadd(v[0], v[2]), d02 = csub(v[0], v[2]);
+    cpx<T> s13 = cadd(v[1], v[3]), d13 = mul_i<SIGN>(csub(v[1], v[3]));
     v[0] = cadd(s02, s13);
     v[1] = cadd(d02, d13);
     v[2] = csub(s02, s13);
@@ -86,15 +89,16 @@ struct Dft<4, SIGN> {
 template <int SIGN>
 struct Dft<6, SIGN> {
   // two length-3 DFTs of the even and odd samples, combined with w6^k
-  __device__ __forceinline__ static void run(cpx<float>* v) {
-    cpx<float> e[3] = {v[0], v[2], v[4]};
-    cpx<float> o[3] = {v[1], v[3], v[5]};
+  template <typename T>
+  __device__ __forceinline__ static void run(cpx<T>* v) {
+    cpx<T> e[3] = {v[0], v[2], v[4]};
+    cpx<T> o[3] = {v[1], v[3], v[5]};
     Dft<3, SIGN>::run(e);
     Dft<3, SIGN>::run(o);
-    const float h = 0.86602540378443864676f;
+    const T h = (T)0.86602540378443864676;
     // w6^1 = 1/2 + SIGN i h, w6^2 = -1/2 + SIGN i h
-    const cpx<float> o1 = {0.5f * o[1].x - SIGN * h * o[1].y, 0.5f * o[1].y + SIGN * h * o[1].x};
-    const cpx<float> o2 = {-0.5f * o[2].x - SIGN * h * o[2].y, -0.5f * o[2].y + SIGN * h * o[2].x};
+    const cpx<T> o1 = {T(0.5) * o[1].x - SIGN * h * o[1].y, T(0.5) * o[1].y + SIGN * h * o[1].x};
+    const cpx<T> o2 = {T(-0.5) * o[2].x - SIGN * h * o[2].y, T(-0.5) * o[2].y + SIGN * h * o[2].x};
     v[0] = cadd(e[0], o[0]);
     v[3] = csub(e[0], o[0]);
     v[1] = cadd(e[1], o1);
@@ -106,9 +110,10 @@ struct Dft<6, SIGN> {
 
 template <int SIGN>
 struct Dft<8, SIGN> {
-  __device__ __forceinline__ static void run(cpx<float>* v) {
-    cpx<float> e[4] = {v[0], v[2], v[4], v[6]};
-    cpx<float> o[4] = {v[1], v[3], v[5], v[7]};
+  template <typename T>
+  __device__ __forceinline__ static void run(cpx<T>* v) {
+    cpx<T> e[4] = {v[0], v[2], v[4], v[6]};
+    cpx<T> o[4] = {v[1], v[3], v[5], v[7]};
     Dft<4, SIGN>::run(e);
     Dft<4, SIGN>::run(o);
     o[1] = rot16<SIGN, 2>(o[1]);
@@ -123,12 +128,44 @@ struct Dft<8, SIGN> {
 };
 
 template <int SIGN>
+struct Dft<9, SIGN> {
+  // 3 x 3: length-3 DFTs over n1 of x[3 n1 + n2], twiddles w9^{n2 k1}, then
+  // length-3 DFTs over n2; output k1 + 3 k2.
+  template <typename T>
+  __device__ __forceinline__ static void run(cpx<T>* v) {
+    // cos and sin of 2 pi k / 9, k = 1, 2, 4
+    const T c1 = (T)0.76604444311897803520, s1 = (T)(SIGN * 0.64278760968653932632);
+    const T c2 = (T)0.17364817766693034885, s2 = (T)(SIGN * 0.98480775301220805937);
+    const T c4 = (T)-0.93969262078590838405, s4 = (T)(SIGN * 0.34202014332566873304);
+    cpx<T> a[3][3];
+#pragma unroll
+    for (int n2 = 0; n2 < 3; ++n2) {
+#pragma unroll
+      for (int n1 = 0; n1 < 3; ++n1) a[n2][n1] = v[3 * n1 + n2];
+      Dft<3, SIGN>::run(a[n2]);
+    }
+    a[1][1] = cmul(a[1][1], {c1, s1});
+    a[1][2] = cmul(a[1][2], {c2, s2});
+    a[2][1] = cmul(a[2][1], {c2, s2});
+    a[2][2] = cmul(a[2][2], {c4, s4});
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) {
+      cpx<T> b[3] = {a[0][k1], a[1][k1], a[2][k1]};
+      Dft<3, SIGN>::run(b);
+#pragma unroll
+      for (int k2 = 0; k2 < 3; ++k2) v[k1 + 3 * k2] = b[k2];
+    }
+  }
+};
+
+template <int SIGN>
 struct Dft<12, SIGN> {
   // Good-Thomas 3 x 4 (coprime factors, so no twiddles between the stages):
   // length-3 DFTs over n1 of x[(4 n1 + 3 n2) mod 12] for each n2, then
   // length-4 DFTs over n2 for each k1, output k = (4 k1 + 9 k2) mod 12.
-  __device__ __forceinline__ static void run(cpx<float>* v) {
-    cpx<float> a[4][3];
+  template <typename T>
+  __device__ __forceinline__ static void run(cpx<T>* v) {
+    cpx<T> a[4][3];
 #pragma unroll
     for (int n2 = 0; n2 < 4; ++n2) {
 #pragma unroll
@@ -137,7 +174,7 @@ struct Dft<12, SIGN> {
     }
 #pragma unroll
     for (int k1 = 0; k1 < 3; ++k1) {
-      cpx<float> b[4] = {a[0][k1], a[1][k1], a[2][k1], a[3][k1]};
+      cpx<T> b[4] = {a[0][k1], a[1][k1], a[2][k1], a[3][k1]};
       Dft<4, SIGN>::run(b);
 #pragma unroll
       for (int k2 = 0; k2 < 4; ++k2) v[(4 * k1 + 9 * k2) % 12] = b[k2];
@@ -151,8 +188,9 @@ struct Dft<16, SIGN> {
   // length-4 DFTs over n2; output k1 + 4 k2.  Fewer operations than halving
   // into two length-8 DFTs (two of the nine twiddles are -i or its multiples
   // of pi/4 and no combining stage of 16 complex additions).
-  __device__ __forceinline__ static void run(cpx<float>* v) {
-    cpx<float> a[4][4];
+  template <typename T>
+  __device__ __forceinline__ static void run(cpx<T>* v) {
+    cpx<T> a[4][4];
 #pragma unroll
     for (int n2 = 0; n2 < 4; ++n2) {
       a[n2][0] = v[n2];
@@ -173,7 +211,7 @@ struct Dft<16, SIGN> {
     a[3][3] = {-a[3][3].x, -a[3][3].y};
 #pragma unroll
     for (int k1 = 0; k1 < 4; ++k1) {
-      cpx<float> b[4] = {a[0][k1], a[1][k1], a[2][k1], a[3][k1]};
+      cpx<T> b[4] = {a[0][k1], a[1][k1], a[2][k1], a[3][k1]};
       Dft<4, SIGN>::run(b);
 #pragma unroll
       for (int k2 = 0; k2 < 4; ++k2) v[k1 + 4 * k2] = b[k2];
@@ -200,15 +238,15 @@ __host__ __device__ constexpr int seq_stride(int len) {
 
 // Twiddle w^{e} from a padded LDS table tw[pad16(t)] = exp(-2 pi i t / (N * TWS)),
 // read at stride TWS (conjugated for SIGN > 0).
-template <int SIGN, int TWS>
-__device__ __forceinline__ cpx<float> twid(const cpx<float>* tw, int e) {
-  cpx<float> w = tw[pad16(e * TWS)];  // tables are stored padded, like the data
+template <int SIGN, int TWS, typename T>
+__device__ __forceinline__ cpx<T> twid(const cpx<T>* tw, int e) {
+  cpx<T> w = tw[pad16(e * TWS)];  // tables are stored padded, like the data
   return SIGN > 0 ? cconj(w) : w;
 }
 
 // Apply the pass twiddles to v[1..R-1] for butterfly phase k.
-template <int N, int R, int P, int SIGN, int TWS = 1>
-__device__ __forceinline__ void pass_twiddle(cpx<float>* v, int k, const cpx<float>* tw) {
+template <int N, int R, int P, int SIGN, int TWS = 1, typename T>
+__device__ __forceinline__ void pass_twiddle(cpx<T>* v, int k, const cpx<T>* tw) {
   if constexpr (P > 1) {
     constexpr int ST = N / (P * R);
 #pragma unroll
@@ -223,12 +261,13 @@ __device__ __forceinline__ void pass_twiddle(cpx<float>* v, int k, const cpx<flo
 // t / NS of sequence t % NS: neighbouring lanes then take the same butterfly
 // of neighbouring sequences, which an odd sequence stride spreads over all
 // banks where the butterflies of one sequence would collide.
-template <int N, int R, int P, int SIGN, int NS, int SS, int NT, int TWS, int PS = 4, bool TW = true, bool SF = false>
-__device__ __forceinline__ void lds_pass(cpx<float>* buf, const cpx<float>* tw, int tid) {
+template <int N, int R, int P, int SIGN, int NS, int SS, int NT, int TWS, int PS = 4, bool TW = true, bool SF = false,
+          typename T>
+__device__ __forceinline__ void lds_pass(cpx<T>* buf, const cpx<T>* tw, int tid) {
   constexpr int NB = N / R;
   constexpr int TOTAL = NS * NB;
   constexpr int PER = (TOTAL + NT - 1) / NT;
-  cpx<float> v[PER][R];
+  cpx<T> v[PER][R];
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
     const int t = tid + q * NT;
@@ -236,7 +275,7 @@ __device__ __forceinline__ void lds_pass(cpx<float>* buf, const cpx<float>* tw, 
       // (t / NS) % NB == t / NS here; the modulo tells the compiler i < NB
       const int s = SF ? t % NS : t / NB, i = SF ? (t / NS) % NB : t % NB;
       const int k = i % P;
-      const cpx<float>* src = buf + s * SS;
+      const cpx<T>* src = buf + s * SS;
 #pragma unroll
       for (int j = 0; j < R; ++j) v[q][j] = src[padp<PS>(i + j * NB)];
       if constexpr (TW) pass_twiddle<N, R, P, SIGN, TWS>(v[q], k, tw);
@@ -250,7 +289,7 @@ __device__ __forceinline__ void lds_pass(cpx<float>* buf, const cpx<float>* tw, 
     if (TOTAL % NT == 0 || t < TOTAL) {
       const int s = SF ? t % NS : t / NB, i = SF ? (t / NS) % NB : t % NB;
       const int k = i % P;
-      cpx<float>* dst = buf + s * SS;
+      cpx<T>* dst = buf + s * SS;
       const int o = (i - k) * R + k;
 #pragma unroll
       for (int j = 0; j < R; ++j) dst[padp<PS>(o + j * P)] = v[q][j];
@@ -263,11 +302,12 @@ template <int... Rs>
 struct RList {};
 
 // Runs the passes of RList in order starting with span P.
-template <int N, int SIGN, int P, int NS, int SS, int NT, int TWS, int PS = 4, bool SF = false>
-__device__ __forceinline__ void lds_passes(cpx<float>*, const cpx<float>*, int, RList<>) {}
+template <int N, int SIGN, int P, int NS, int SS, int NT, int TWS, int PS = 4, bool SF = false, typename T>
+__device__ __forceinline__ void lds_passes(cpx<T>*, const cpx<T>*, int, RList<>) {}
 
-template <int N, int SIGN, int P, int NS, int SS, int NT, int TWS, int PS = 4, bool SF = false, int R, int... Rest>
-__device__ __forceinline__ void lds_passes(cpx<float>* buf, const cpx<float>* tw, int tid, RList<R, Rest...>) {
+template <int N, int SIGN, int P, int NS, int SS, int NT, int TWS, int PS = 4, bool SF = false, int R, int... Rest,
+          typename T>
+__device__ __forceinline__ void lds_passes(cpx<T>* buf, const cpx<T>* tw, int tid, RList<R, Rest...>) {
   lds_pass<N, R, P, SIGN, NS, SS, NT, TWS, PS, true, SF>(buf, tw, tid);
   lds_passes<N, SIGN, P * R, NS, SS, NT, TWS, PS, SF>(buf, tw, tid, RList<Rest...>{});
 }

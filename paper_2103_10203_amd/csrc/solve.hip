@@ -18,7 +18,7 @@
 #include <vector>
 
 #include "dft_kernels.h"
-#include "solve_fast.h"
+#include "solve_cp.h"
 
 using namespace mor_k;
 
@@ -140,6 +140,11 @@ struct Group {
   int gidx = 0;  // position of the group (active count slot)
   int* d_alist = nullptr;  // this group's segment of the active list
   bool fast_row = false, fast_col = false;
+  bool cp_row = false;   // row passes on the component-parallel kernels throughout
+  bool cp_few = false;   // iteration rows on their form for few workgroups
+  int rb_limit = 1, cb_limit = 1;  // blocks the scratch limit of a no-allocation solve counts
+  int rb_iter = 1;       // rows per workgroup of the iteration's row kernel
+  bool cp_col = false;   // columns of the lengths outside ColCfg (and FP64)
   int* d_list = nullptr;
 };
 
@@ -186,6 +191,14 @@ int row_variants(int C, int nh) {
   }
 }
 
+// Default row variant: with the plastic state in registers the radix-4
+// register passes keep more waves resident (measured on J2 load paths).
+int row_default(int C, int nh, bool j2) {
+  if (j2 && C == 3 && nh == 256) return 4;
+  if (j2 && C == 3 && nh == 192) return 2;
+  return 0;
+}
+
 // Row variant of a size: the tuned one, else the default.  The J2 law holds
 // more registers per point (state in, state out), so with J2 phases a size may
 // default to a variant with a smaller register pass (measured on the 512^2
@@ -193,12 +206,7 @@ int row_variants(int C, int nh) {
 int row_variant(int C, int nh, bool j2 = false) {
   std::lock_guard<std::mutex> lk(g_var_mu);
   auto it = g_row_var.find({C, nh});
-  if (it != g_row_var.end()) return it->second;
-  // with the plastic state in registers the radix-4 register passes keep
-  // more waves resident than the defaults (measured on J2 load paths)
-  if (j2 && C == 3 && nh == 256) return 4;
-  if (j2 && C == 3 && nh == 192) return 2;
-  return 0;
+  return it != g_row_var.end() ? it->second : row_default(C, nh, j2);
 }
 
 int fast_rb(int C, int nh, int v) {
@@ -329,6 +337,32 @@ mor_status cx_get(SolveCtx& cx, const char* name, size_t count, T** out) {
   }
   *out = reinterpret_cast<T*>(cx.arena + cx.arena_used);
   cx.arena_used += bytes;
+  return MOR_OK;
+}
+
+// Partial sums of the residual (n) and the stress (S n).  A no-allocation
+// solve takes them from the array's own part for them and counts `limit`
+// blocks against MOR_NOALLOC_SCRATCH_BYTES: the blocks of the runtime-radix
+// kernels, larger and so fewer than those of the compile-time ones, which set
+// the sizes that fit.  The part's size covers every call that fits: its bytes
+// are at most 0.42 of the transform lines'.
+constexpr size_t kNoallocPartBytes = MOR_NOALLOC_SCRATCH_BYTES / 7 * 3;
+mor_status get_parts(SolveCtx& cx, size_t n, size_t limit) {
+  mor_status s;
+  if (!cx.noalloc || n == limit) {
+    if ((s = cx_get(cx, "part", n, &cx.d_part)) != MOR_OK) return s;
+    return cx_get(cx, "sigpart", n * cx.S, &cx.d_sigpart);
+  }
+  if ((s = cx_get(cx, "part", limit, &cx.d_part)) != MOR_OK) return s;
+  if ((s = cx_get(cx, "sigpart", limit * cx.S, &cx.d_sigpart)) != MOR_OK) return s;
+  if (n <= limit) return MOR_OK;
+  if (n * (1 + cx.S) * sizeof(double) > kNoallocPartBytes) {
+    mor_set_error("mor_solve_noalloc: the partial sums need more than their part of the scratch array; use fewer "
+                  "RVEs per call");
+    return MOR_E_INVALID_ARG;
+  }
+  cx.d_part = reinterpret_cast<double*>(cx.arena + MOR_NOALLOC_SCRATCH_BYTES);
+  cx.d_sigpart = cx.d_part + n;
   return MOR_OK;
 }
 
@@ -672,9 +706,12 @@ void col_persist(SolveCtx& cx, Group& g) {
   }
 }
 
-// 3D axis-1 transform of a group: specialised kernels for n1 = 32/64/128,
-// the generic runtime-radix kernel otherwise.
-bool has_fast_mid(int n1) { return n1 == 32 || n1 == 64 || n1 == 128; }
+// 3D axis-1 transform of a group: specialised kernels for the lengths of
+// MidCfg, the generic runtime-radix kernel otherwise.
+bool has_fast_mid(int n1) {
+  return n1 == 24 || n1 == 32 || n1 == 36 || n1 == 48 || n1 == 54 || n1 == 64 || n1 == 72 || n1 == 96 || n1 == 108 ||
+         n1 == 128;
+}
 
 template <int N1, int DIR>
 void go_mid_fast(SolveCtx& cx, Group& g, int check_active) {
@@ -687,6 +724,13 @@ template <int DIR>
 void launch_mid(SolveCtx& cx, Group& g, int check_active) {
   if (has_fast_mid(g.n1) && !cx.fp64) {
     switch (g.n1) {
+      case 24: go_mid_fast<24, DIR>(cx, g, check_active); break;
+      case 36: go_mid_fast<36, DIR>(cx, g, check_active); break;
+      case 48: go_mid_fast<48, DIR>(cx, g, check_active); break;
+      case 54: go_mid_fast<54, DIR>(cx, g, check_active); break;
+      case 72: go_mid_fast<72, DIR>(cx, g, check_active); break;
+      case 96: go_mid_fast<96, DIR>(cx, g, check_active); break;
+      case 108: go_mid_fast<108, DIR>(cx, g, check_active); break;
       case 32: go_mid_fast<32, DIR>(cx, g, check_active); break;
       case 64: go_mid_fast<64, DIR>(cx, g, check_active); break;
       default: go_mid_fast<128, DIR>(cx, g, check_active); break;
@@ -720,13 +764,44 @@ void col_fast(SolveCtx& cx, Group& g, const cpx<float>* warm) {
   }
 }
 
+CpArgs cp_args(SolveCtx& cx, Group& g) {
+  CpArgs a{};
+  a.st = cx.st;
+  a.plans = cx.d_plans;
+  a.list = g.d_list;
+  a.nrve = (int)g.rves.size();
+  a.state = cx.d_st;
+  a.yl = cx.d_yl;
+  a.yc = cx.d_yc;
+  a.coef = cx.d_coef;
+  a.ebar = cx.d_ebar;
+  a.off = cx.off;
+  a.part = cx.d_part;
+  a.mat = &cx.mat;
+  a.mat64 = &cx.mat64;
+  a.jstate = cx.d_jstate;
+  a.sigpart = cx.d_sigpart;
+  return a;
+}
+
+// A dispatch without the kernel that setup() chose: an error, never a
+// silently missing launch.
+mor_status no_kernel(const char* what) {
+  mor_set_error(std::string("no ") + what + " kernel for this length");
+  return MOR_E_UNSUPPORTED;
+}
+
 template <int C>
 mor_status launch_init(SolveCtx& cx, Group& g, const cpx<float>* warm) {
   const size_t shc = (size_t)(g.n0 + 2 * C * g.cb * g.n0) * sizeof(cpx<float>);
   dim3 grid((g.ncol_max + g.cb - 1) / g.cb, (unsigned)g.rves.size());
   hipEvent_t a{};
   ev_begin(cx, PK_INIT, &a);
-  if (cx.fp64)
+  if (g.cp_col) {
+    CpArgs ca = cp_args(cx, g);
+    ca.warm = warm;
+    if (!cp_col(C, g.n0, cx.fp64, CP_INIT, g.ncol_max, ca)) return no_kernel("col(init)");
+  } else if (cx.fp64)
     k_col<C, MODE_INIT, double, MatDev64><<<grid, 256, 2 * shc, cx.st>>>(
         cx.d_plans, g.d_list, cx.d_st, cx.d_ebar, cx.yc64(), cx.coef64(), warm, cx.off, cx.d_part, cx.mat64, g.cb);
   else if (g.fast_col)
@@ -815,8 +890,8 @@ mor_status launch_row64(SolveCtx& cx, Group& g, dim3 gr, size_t shm, float* eps,
 // (4096) 3.26 / 3.25 ms, eight of 128^3 (8192) 9.15 / 9.02 ms.
 constexpr int64_t kRowDecidesMax = 2048;
 bool row_decides(const SolveCtx& cx, const Group& g, int rows) {
-  return g.fast_row && !cx.persist && !cx.dft &&
-         (int64_t)((rows + g.rb - 1) / g.rb) * (int64_t)g.rves.size() <= kRowDecidesMax;
+  return (g.cp_row || (g.fast_row && !cx.persist)) && !cx.dft &&
+         (int64_t)((rows + g.rb_iter - 1) / g.rb_iter) * (int64_t)g.rves.size() <= kRowDecidesMax;
 }
 
 // One iteration of a group; first and last say whether it opens or ends a
@@ -839,7 +914,11 @@ mor_status launch_iter(SolveCtx& cx, Group& g, bool first, bool last) {
   ev_begin(cx, PK_ROW, &a);
   if (cx.dft)
     launch_dft_stage<C, MAT>(cx, g, rows, nlen);
-  else if (cx.fp64) {
+  else if (g.cp_row || (g.cp_few && !pers)) {
+    CpArgs a = cp_args(cx, g);
+    if (!first && row_decides(cx, g, rows)) a.dec = dec;
+    if (!cp_row(C, nh, cx.fp64, MAT == MAT_J2, CP_ITER, rows, a)) return no_kernel("row");
+  } else if (cx.fp64) {
     const mor_status s64 = launch_row64<C, MODE_ITER, MAT>(cx, g, gr, 2 * shr, nullptr, nullptr);
     if (s64 != MOR_OK) return s64;
   } else if (g.fast_row && pers)
@@ -860,7 +939,9 @@ mor_status launch_iter(SolveCtx& cx, Group& g, bool first, bool last) {
   const size_t shc = (size_t)(g.n0 + 2 * C * g.cb * g.n0) * sizeof(cpx<float>);
   dim3 gc((g.ncol_max + g.cb - 1) / g.cb, (unsigned)g.rves.size());
   ev_begin(cx, PK_COL, &a);
-  if (cx.fp64)
+  if (g.cp_col) {
+    if (!cp_col(C, g.n0, cx.fp64, CP_ITER, g.ncol_max, cp_args(cx, g))) return no_kernel("col");
+  } else if (cx.fp64)
     k_col<C, MODE_ITER, double, MatDev64><<<gc, 256, 2 * shc, cx.st>>>(
         cx.d_plans, g.d_list, cx.d_st, cx.d_ebar, cx.yc64(), cx.coef64(), nullptr, cx.off, cx.d_part, cx.mat64, g.cb);
   else if (g.fast_col && pers)
@@ -903,6 +984,11 @@ mor_status launch_final(SolveCtx& cx, Group& g, float* eps, float* sig) {
     dim3 gp((rows + kDftRb - 1) / kDftRb, (unsigned)g.rves.size());
     k_dft_point<C, MODE_FINAL, MAT><<<gp, 256, 0, cx.st>>>(cx.d_plans, g.d_list, cx.d_st, cx.off, cx.mat, cx.d_dfte,
                                                            cx.d_jstate, eps, sig, cx.d_sigpart, kDftRb);
+  } else if (g.cp_row) {
+    CpArgs a2 = cp_args(cx, g);
+    a2.eps = eps;
+    a2.sig = sig;
+    if (!cp_row(C, nh, cx.fp64, MAT == MAT_J2, CP_FINAL, rows, a2)) return no_kernel("row(final)");
   } else if (cx.fp64) {
     const mor_status s64 = launch_row64<C, MODE_FINAL, MAT>(cx, g, gr, 2 * shr, eps, sig);
     if (s64 != MOR_OK) return s64;
@@ -989,6 +1075,21 @@ std::atomic<int64_t>& subbatch_min_rves() {
   return v;
 }
 
+// Whether a group's row passes run on the component-parallel kernels: the
+// lengths without a row_fast kernel (and every built length in FP64), unless
+// an RVE's lines reach the 2^31 bytes their 32-bit offsets cover.
+bool use_cp_row(const SolveCtx& cx, const Group& g, int rows, int nh) {
+  const int64_t es = cx.fp64 ? sizeof(cpx<double>) : sizeof(cpx<float>);
+  return !cx.dft && cp_row_only(cx.C, nh, cx.fp64) && (int64_t)cx.C * g.nlast_max * rows * es < (1LL << 31);
+}
+
+// Row kernel of a group's iterations (the final pass keeps g.rb).
+void choose_row(const SolveCtx& cx, Group& g) {
+  const int nlen = g.ndim == 2 ? g.n1 : g.n2;
+  const int rows = g.ndim == 2 ? g.n0 : g.n0 * g.n1;
+  g.rb_iter = g.rb;
+}
+
 // Prepare the context: plan table, groups, offsets, states.
 mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::vector<int>& plan_of,
                  const double* ebar, int64_t B, const mor_phase* phase, double tol, const mor_solve_opts* opts,
@@ -1055,7 +1156,7 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
   // offsets
   std::vector<int64_t> offs(5 * B);
   std::vector<int> nblk(B);
-  int64_t yl = 0, yc = 0, co = 0, fo = 0, pa = 0;
+  int64_t yl = 0, yc = 0, co = 0, fo = 0, pa = 0, pa_limit = 0;
   cx.coef_off_h.resize(B);
   cx.field_off_h.resize(B);
   cx.ncoef_h.resize(B);
@@ -1084,14 +1185,22 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
     } else {
       g.rb = rows_per_block(cx.C, nlen, es);
     }
-    if (g.fast_col) {
+    g.rb_limit = g.fast_row || cx.dft ? g.rb : std::min(g.rb, rows);
+    g.cb_limit = g.fast_col ? fast_cb(cx.C, g.n0, std::min(col_variant(cx.C, g.n0), col_variants(cx.C, g.n0) - 1))
+                            : cols_per_block(cx.C, g.n0, es);
+    g.cp_row = use_cp_row(cx, g, rows, nlen / 2);
+    if (g.cp_row) g.rb = cp_row_rb(cx.C, nlen / 2, cx.fp64, cx.j2);
+    g.cp_col = cp_col_cb(cx.C, g.n0, cx.fp64) > 0;
+    if (g.cp_col) {
+      g.cb = cp_col_cb(cx.C, g.n0, cx.fp64);
+    } else if (g.fast_col) {
       g.cvar = std::min(col_variant(cx.C, g.n0), col_variants(cx.C, g.n0) - 1);
       g.cb = fast_cb(cx.C, g.n0, g.cvar);
     } else {
       g.cb = cols_per_block(cx.C, g.n0, es);
     }
     g.xb = g.ndim == 3 ? cols_per_block(cx.C, g.n1, es) : 1;
-    if (!g.fast_row && !cx.dft) g.rb = std::min(g.rb, rows);
+    if (!g.fast_row && !g.cp_row && !cx.dft) g.rb = std::min(g.rb, rows);
   }
   // Sub-batches: a group's RVEs are cut into runs whose transform lines fit
   // in the device's last-level cache, and the iteration loop runs the chunk
@@ -1133,6 +1242,8 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
     }
     cx.groups.swap(split);
   }
+  // the iteration's row kernel: chosen per sub-batch, by its size
+  for (auto& g : cx.groups) choose_row(cx, g);
   std::vector<int> gof(B);
   for (size_t gi = 0; gi < cx.groups.size(); ++gi)
     for (int b : cx.groups[gi].rves) gof[b] = (int)gi;
@@ -1159,6 +1270,9 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
     const int nrb = (rows + g.rb - 1) / g.rb;
     const int ncb = (p->dev.ncol + g.cb - 1) / g.cb;
     pa += std::max(nrb, ncb);
+    pa_limit += (g.cp_row || g.cp_col) ? std::max((rows + g.rb_limit - 1) / g.rb_limit,
+                                              (p->dev.ncol + g.cb_limit - 1) / g.cb_limit)
+                                   : std::max(nrb, ncb);
     nblk[b] = nrb;
   }
   int64_t* d_offs;
@@ -1179,8 +1293,7 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
   }
   if ((s = cx_get(cx, "coef", (size_t)co * ew, &cx.d_coef)) != MOR_OK) return s;
   if (cx.dft && (s = cx_get(cx, "dfte", (size_t)fo * cx.C, &cx.d_dfte)) != MOR_OK) return s;
-  if ((s = cx_get(cx, "part", (size_t)pa, &cx.d_part)) != MOR_OK) return s;
-  if ((s = cx_get(cx, "sigpart", (size_t)pa * cx.S, &cx.d_sigpart)) != MOR_OK) return s;
+  if ((s = get_parts(cx, (size_t)pa, (size_t)pa_limit)) != MOR_OK) return s;
   if ((s = cx_get(cx, "eff", (size_t)B * cx.S, &cx.d_eff)) != MOR_OK) return s;
   if ((s = cx_get(cx, "active", 1, &cx.d_active)) != MOR_OK) return s;
   if ((s = cx_get(cx, "ebar", (size_t)B * cx.C, &cx.d_ebar)) != MOR_OK) return s;
@@ -1545,7 +1658,7 @@ extern "C" mor_status mor_solve(mor_plan_t plan, const double* macro_strain, int
 // only a stand-in for the symbol: the device address is looked up once per
 // device with hipGetSymbolAddress (each GPU holds its own copy) and only
 // that address is passed to kernels and copies.
-static __device__ __align__(256) unsigned char scratch[MOR_NOALLOC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[MOR_NOALLOC_SCRATCH_BYTES + kNoallocPartBytes];
 
 namespace {
 std::mutex g_scratch_mu;

@@ -493,33 +493,44 @@ template <> struct ColCfg<6, 128, 0> { static constexpr int RF = 16, CB = 4; usi
 template <> struct ColCfg<6, 128, 1> { static constexpr int RF = 8,  CB = 2; using FA = RList<4, 4>; };
 template <> struct ColVar<6, 128> { static constexpr int count = 2; };
 
-template <int C, int N0, int V>
-constexpr int col_threads() {
-  return ColCfg<C, N0, V>::CB * C * (N0 / ColCfg<C, N0, V>::RF);
+// Threads of a workgroup: one per sequence and butterfly of the register
+// pass, filled up to whole wavefronts (the extra threads take part in the
+// strided loops and barriers only).
+constexpr int whole_waves(int n) { return (n + 63) / 64 * 64; }
+template <int C, int N0, typename Cfg>
+constexpr int col_nt() {
+  return whole_waves(Cfg::CB * C * (N0 / Cfg::RF));
 }
 template <int N0>
 constexpr int col_ss() {
   return fftr::seq_stride(N0);
 }
+template <int C, int N0, typename Cfg, typename T = float>
+constexpr size_t col_lds() {
+  return (size_t)(pad16(N0 - 1) + 1 + C * Cfg::CB * col_ss<N0>()) * sizeof(cpx<T>);
+}
+template <int C, int N0, int V>
+constexpr int col_threads() {
+  return col_nt<C, N0, ColCfg<C, N0, V>>();
+}
 template <int C, int N0, int V>
 constexpr size_t col_lds_bytes() {
-  return (size_t)(pad16(N0 - 1) + 1 + C * ColCfg<C, N0, V>::CB * col_ss<N0>()) * sizeof(cpx<float>);
+  return col_lds<C, N0, ColCfg<C, N0, V>>();
 }
 
 // One block of columns (tile) of one RVE.
-template <int C, int N0, int V, int MODE>
+template <int C, int N0, typename Cfg, int MODE, typename T = float, typename MT = MatDev>
 __device__ __forceinline__ void col_tile(const PlanDev* __restrict__ plans, const int b, const int tile,
                                          RveState* __restrict__ st, const double* __restrict__ ebar,
-                                         cpx<float>* __restrict__ Yc, cpx<float>* __restrict__ coef,
+                                         cpx<T>* __restrict__ Yc, cpx<T>* __restrict__ coef,
                                          const cpx<float>* __restrict__ warm, const Offs& off,
-                                         double* __restrict__ part, const MatDev& mat, const int tid) {
-  using Cfg = ColCfg<C, N0, V>;
+                                         double* __restrict__ part, const MT& mat, const int tid) {
   constexpr int RF = Cfg::RF, CB = Cfg::CB;
   constexpr int TS = N0 / RF;
-  constexpr int NT = CB * C * TS;
+  constexpr int NA = CB * C * TS;  // threads with a sequence
+  constexpr int NT = whole_waves(NA);
   constexpr int NSEQ = C * CB;
   constexpr int SS = col_ss<N0>();
-  static_assert(NT % 64 == 0, "workgroups are whole wavefronts");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   __shared__ int coff[CB + 1];
   __shared__ double cwt[CB];  // Parseval weight of each column of the block (1 or 2)
@@ -529,11 +540,11 @@ __device__ __forceinline__ void col_tile(const PlanDev* __restrict__ plans, cons
   const int j0 = tile * CB;
   if (j0 >= ncol) return;
   const int ncb = min(CB, ncol - j0);
-  cpx<float>* tw = reinterpret_cast<cpx<float>*>(smem_raw);
+  cpx<T>* tw = reinterpret_cast<cpx<T>*>(smem_raw);
   // one buffer: the forward result tau^, then (after the Green step has read
   // it) the new coefficients and the inverse transform
-  cpx<float>* buf = tw + pad16(N0 - 1) + 1;
-  for (int t = tid; t < N0; t += NT) tw[pad16(t)] = P.tw0[t];
+  cpx<T>* buf = tw + pad16(N0 - 1) + 1;
+  for (int t = tid; t < N0; t += NT) tw[pad16(t)] = PT<T>::tw0(P)[t];
   if (tid <= CB) coff[tid] = P.col_off[j0 + min(tid, ncb)];
   if (MODE == MODE_ITER && tid < ncb) {
     const int kl = P.last_k[P.col_last[j0 + tid]];
@@ -541,38 +552,42 @@ __device__ __forceinline__ void col_tile(const PlanDev* __restrict__ plans, cons
   }
   // prefetch this thread's first pattern entry (its loads overlap the FFT)
   const int ncoef = P.ncoef;
-  cpx<float>* co = coef + off.coef[b];
+  const T* __restrict__ coef_n = PT<T>::coef_n(P);
+  cpx<T>* co = coef + off.coef[b];
   const int ebeg = P.col_off[j0], eend = P.col_off[j0 + ncb];
   int pk0 = 0;
   uint8_t pfl = 0;
-  float pn[3] = {0.f, 0.f, 0.f};
-  cpx<float> pold[C];
+  T pn[3] = {T(0), T(0), T(0)};
+  cpx<T> pold[C];
   if (ebeg + tid < eend) {
     const int e = ebeg + tid;
     pk0 = P.coef_k0[e];
     pfl = P.coef_flag[e];
-    pn[0] = P.coef_n[3 * e];
-    pn[1] = P.coef_n[3 * e + 1];
-    pn[2] = P.coef_n[3 * e + 2];
+    pn[0] = coef_n[3 * e];
+    pn[1] = coef_n[3 * e + 1];
+    pn[2] = coef_n[3 * e + 2];
     if (MODE == MODE_ITER) {
 #pragma unroll
       for (int c = 0; c < C; ++c) pold[c] = co[(int64_t)c * ncoef + e];
     }
   }
-  cpx<float>* Y = Yc + off.yc[b];
+  cpx<T>* Y = Yc + off.yc[b];
   const int64_t cstride = (int64_t)ncol * N0;
   const int s = tid / TS, i = tid % TS;  // sequence s = c * CB + jj
   const int c_s = s / CB, jj_s = s % CB;
-  const bool col_live = jj_s < ncb;
-  cpx<float>* yline = Y + c_s * cstride + (int64_t)(j0 + jj_s) * N0;
+  const bool seq_live = NA == NT || s < NSEQ;
+  const bool col_live = seq_live && jj_s < ncb;
+  cpx<T>* yline = Y + c_s * cstride + (int64_t)(j0 + jj_s) * N0;
   if (MODE == MODE_ITER) {
-    cpx<float> v[RF];
+    cpx<T> v[RF];
 #pragma unroll
-    for (int j = 0; j < RF; ++j) v[j] = col_live ? yline[i + j * TS] : cpx<float>{0.f, 0.f};
+    for (int j = 0; j < RF; ++j) v[j] = col_live ? yline[i + j * TS] : cpx<T>{T(0), T(0)};
     Dft<RF, -1>::run(v);
-    cpx<float>* dst = buf + s * SS;
+    if (seq_live) {
+      cpx<T>* dst = buf + s * SS;
 #pragma unroll
-    for (int j = 0; j < RF; ++j) dst[pad16(i * RF + j)] = v[j];
+      for (int j = 0; j < RF; ++j) dst[pad16(i * RF + j)] = v[j];
+    }
     __syncthreads();
     fftr::lds_passes<N0, -1, RF, NSEQ, SS, NT, 1>(buf, tw, tid, typename Cfg::FA{});
   } else {
@@ -583,10 +598,10 @@ __device__ __forceinline__ void col_tile(const PlanDev* __restrict__ plans, cons
   // registers; once every entry has read tau^, the whole buffer is cleared
   // (unconditional stores) and the entries write their coefficients.
   constexpr int EPT = (CB * N0 + NT - 1) / NT;
-  const float invN = P.inv_N;
+  const T invN = PT<T>::inv_N(P);
   double dsum = 0.0;
   int kpos[EPT];
-  float kre[EPT][C], kim[EPT][C];
+  T kre[EPT][C], kim[EPT][C];
 #pragma unroll
   for (int u = 0; u < EPT; ++u) {
     kpos[u] = -1;
@@ -597,52 +612,52 @@ __device__ __forceinline__ void col_tile(const PlanDev* __restrict__ plans, cons
     const bool first = u == 0;
     const int k0 = first ? pk0 : P.coef_k0[e];
     const uint8_t fl = first ? pfl : P.coef_flag[e];
-    float nr_[C], ni_[C];
+    T nr_[C], ni_[C];
     if (fl & COEF_ZERO) {
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        nr_[c] = (float)((double)P.N * ebar[(int64_t)b * C + c]);
-        ni_[c] = 0.f;
+        nr_[c] = (T)((double)P.N * ebar[(int64_t)b * C + c]);
+        ni_[c] = T(0);
       }
     } else if (fl & COEF_DEAD) {
 #pragma unroll
-      for (int c = 0; c < C; ++c) nr_[c] = ni_[c] = 0.f;
+      for (int c = 0; c < C; ++c) nr_[c] = ni_[c] = T(0);
     } else if (MODE == MODE_ITER) {
-      float tr_[C], ti_[C];
+      T tr_[C], ti_[C];
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const cpx<float> w = buf[(c * CB + jj) * SS + pad16(k0)];
+        const cpx<T> w = buf[(c * CB + jj) * SS + pad16(k0)];
         tr_[c] = w.x;
         ti_[c] = w.y;
       }
-      float nv[3];
+      T nv[3];
       if (first) {
         nv[0] = pn[0]; nv[1] = pn[1]; nv[2] = pn[2];
       } else {
-        nv[0] = P.coef_n[3 * e]; nv[1] = P.coef_n[3 * e + 1]; nv[2] = P.coef_n[3 * e + 2];
+        nv[0] = coef_n[3 * e]; nv[1] = coef_n[3 * e + 1]; nv[2] = coef_n[3 * e + 2];
       }
-      green<C>(nv, tr_, nr_, mat.g_inv_mu0, mat.g_k);
-      green<C>(nv, ti_, ni_, mat.g_inv_mu0, mat.g_k);
+      green<C, T>(nv, tr_, nr_, mat.g_inv_mu0, mat.g_k);
+      green<C, T>(nv, ti_, ni_, mat.g_inv_mu0, mat.g_k);
     } else {
       if (warm && st[b].warm_ok) {
-        float wr[C], wi[C];
+        T wr[C], wi[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
           const cpx<float> w = warm[off.coef[b] + (int64_t)c * ncoef + e];
           wr[c] = w.x;
           wi[c] = w.y;
         }
-        float nv[3];
+        T nv[3];
         if (first) {
           nv[0] = pn[0]; nv[1] = pn[1]; nv[2] = pn[2];
         } else {
-          nv[0] = P.coef_n[3 * e]; nv[1] = P.coef_n[3 * e + 1]; nv[2] = P.coef_n[3 * e + 2];
+          nv[0] = coef_n[3 * e]; nv[1] = coef_n[3 * e + 1]; nv[2] = coef_n[3 * e + 2];
         }
-        project_compatible<C>(nv, wr, nr_, mat);
-        project_compatible<C>(nv, wi, ni_, mat);
+        project_compatible<C, T>(nv, wr, nr_, mat);
+        project_compatible<C, T>(nv, wi, ni_, mat);
       } else {
 #pragma unroll
-        for (int c = 0; c < C; ++c) nr_[c] = ni_[c] = 0.f;
+        for (int c = 0; c < C; ++c) nr_[c] = ni_[c] = T(0);
       }
     }
     if (MODE == MODE_ITER) {
@@ -650,7 +665,7 @@ __device__ __forceinline__ void col_tile(const PlanDev* __restrict__ plans, cons
       double d2 = 0.0;
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        const cpx<float> old = first ? pold[c] : co[(int64_t)c * ncoef + e];
+        const cpx<T> old = first ? pold[c] : co[(int64_t)c * ncoef + e];
         const double dr = (double)nr_[c] - (double)old.x, di = (double)ni_[c] - (double)old.y;
         d2 += (double)comp_weight<C>(c) * (dr * dr + di * di);
       }
@@ -672,9 +687,11 @@ __device__ __forceinline__ void col_tile(const PlanDev* __restrict__ plans, cons
     // thread indices re-derived here rather than kept live across the Green step
     const int t2 = opaque_tid();
     const int s2 = t2 / TS, i2 = t2 % TS;
-    cpx<float>* seqb = buf + s2 * SS;
+    if (NA == NT || s2 < NSEQ) {
+      cpx<T>* seqb = buf + s2 * SS;
 #pragma unroll
-    for (int m = 0; m < RF; ++m) seqb[pad16(i2 + m * TS)] = {0.f, 0.f};
+      for (int m = 0; m < RF; ++m) seqb[pad16(i2 + m * TS)] = {T(0), T(0)};
+    }
   }
   __syncthreads();
 #pragma unroll
@@ -686,9 +703,9 @@ __device__ __forceinline__ void col_tile(const PlanDev* __restrict__ plans, cons
   __syncthreads();
   // step d), axis 0: inverse passes, the last one straight to global memory
   fftr::lds_passes<N0, +1, 1, NSEQ, SS, NT, 1>(buf, tw, tid, typename fftr::Rev<typename Cfg::FA, RList<>>::type{});
-  {
-    cpx<float> v[RF];
-    const cpx<float>* src = buf + s * SS;
+  if (seq_live) {
+    cpx<T> v[RF];
+    const cpx<T>* src = buf + s * SS;
 #pragma unroll
     for (int j = 0; j < RF; ++j) v[j] = src[pad16(i + j * TS)];
     fftr::pass_twiddle<N0, RF, TS, +1>(v, i, tw);
@@ -713,7 +730,7 @@ __global__ __launch_bounds__((col_threads<C, N0, V>())) __attribute__((amdgpu_wa
     const PlanDev* __restrict__ plans, const int* __restrict__ rve_list, RveState* __restrict__ st,
     const double* __restrict__ ebar, cpx<float>* __restrict__ Yc, cpx<float>* __restrict__ coef,
     const cpx<float>* __restrict__ warm, Offs off, double* __restrict__ part, MatDev mat) {
-  col_tile<C, N0, V, MODE>(plans, rve_list[blockIdx.y], blockIdx.x, st, ebar, Yc, coef, warm, off, part, mat,
+  col_tile<C, N0, ColCfg<C, N0, V>, MODE>(plans, rve_list[blockIdx.y], blockIdx.x, st, ebar, Yc, coef, warm, off, part, mat,
                            threadIdx.x);
 }
 
@@ -727,13 +744,13 @@ __global__ __launch_bounds__((col_threads<C, N0, V>())) void k_col_persist(
   for (int q = blockIdx.x; q < nitems; q += gridDim.x) {
     const int b = __builtin_amdgcn_readfirstlane(alist[q / ntiles]);
     const int tile = __builtin_amdgcn_readfirstlane(q % ntiles);
-    col_tile<C, N0, V, MODE_ITER>(plans, b, tile, st, ebar, Yc, coef, nullptr, off, part, mat, opaque_tid());
+    col_tile<C, N0, ColCfg<C, N0, V>, MODE_ITER>(plans, b, tile, st, ebar, Yc, coef, nullptr, off, part, mat, opaque_tid());
     __syncthreads();
   }
 }
 
 // 3D axis-1 kernels (between the row and the column stages), compile-time
-// specialised for n1 = 32 / 64 / 128: per workgroup XB consecutive values of
+// specialised for the lengths of MidCfg: per workgroup XB consecutive values of
 // x0 of one strain component c for one last-axis frequency j2 of one RVE
 // (blockIdx.x = c * ceil(n0 / XB) + x0 block), N1/RF threads per sequence.
 // Forward: lines of Yl along x1 -> FFT (first pass from HBM into registers,
@@ -743,13 +760,20 @@ __global__ __launch_bounds__((col_threads<C, N0, V>())) void k_col_persist(
 // access a 128-byte run; the XB lines read or written are adjacent in Yl.
 template <int N1>
 struct MidCfg;
+template <> struct MidCfg<24>  { static constexpr int RF = 4, XB = 16; using FA = RList<6>; };
+template <> struct MidCfg<36>  { static constexpr int RF = 6, XB = 16; using FA = RList<6>; };
+template <> struct MidCfg<48>  { static constexpr int RF = 6, XB = 16; using FA = RList<8>; };
+template <> struct MidCfg<54>  { static constexpr int RF = 6, XB = 16; using FA = RList<9>; };
+template <> struct MidCfg<72>  { static constexpr int RF = 8, XB = 16; using FA = RList<9>; };
+template <> struct MidCfg<96>  { static constexpr int RF = 8, XB = 16; using FA = RList<12>; };
+template <> struct MidCfg<108> { static constexpr int RF = 9, XB = 16; using FA = RList<12>; };
 template <> struct MidCfg<32>  { static constexpr int RF = 8, XB = 16; using FA = RList<4>; };
 template <> struct MidCfg<64>  { static constexpr int RF = 8, XB = 16; using FA = RList<8>; };
 template <> struct MidCfg<128> { static constexpr int RF = 8, XB = 16; using FA = RList<4, 4>; };
 
 template <int N1>
 constexpr int mid_threads() {
-  return MidCfg<N1>::XB * (N1 / MidCfg<N1>::RF);
+  return whole_waves(MidCfg<N1>::XB * (N1 / MidCfg<N1>::RF));
 }
 template <int N1>
 constexpr size_t mid_lds_bytes() {
@@ -765,7 +789,6 @@ __global__ __launch_bounds__((mid_threads<N1>())) void k_mid_fast(
   constexpr int TS = N1 / RF;
   constexpr int NT = mid_threads<N1>();
   constexpr int SS = fftr::seq_stride(N1);
-  static_assert(NT % 64 == 0, "workgroups are whole wavefronts");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int tid = threadIdx.x;
   const int b = rve_list[blockIdx.z];
@@ -788,7 +811,8 @@ __global__ __launch_bounds__((mid_threads<N1>())) void k_mid_fast(
   const int ja = P.last_off[j2], jb = P.last_off[j2 + 1];
   const int ng = jb - ja;
   const int s = tid / TS, i = tid % TS;  // sequence s = x0 - x00
-  const bool live = s < nx;
+  const bool live = s < nx;         // false for the threads that fill up the last wavefront
+  const bool seq_live = XB * TS == NT || s < XB;
   cpx<float>* line = L + (int64_t)j2 * rows + (int64_t)(x00 + s) * N1;
   if (DIR < 0) {
     cpx<float> v[RF];
@@ -796,9 +820,11 @@ __global__ __launch_bounds__((mid_threads<N1>())) void k_mid_fast(
     for (int j = 0; j < RF; ++j) v[j] = live ? line[i + j * TS] : cpx<float>{0.f, 0.f};
     __syncthreads();  // twiddle table
     Dft<RF, -1>::run(v);
-    cpx<float>* dst = buf + s * SS;
+    if (seq_live) {
+      cpx<float>* dst = buf + s * SS;
 #pragma unroll
-    for (int j = 0; j < RF; ++j) dst[pad16(i * RF + j)] = v[j];
+      for (int j = 0; j < RF; ++j) dst[pad16(i * RF + j)] = v[j];
+    }
     __syncthreads();
     fftr::lds_passes<N1, -1, RF, XB, SS, NT, 1>(buf, tw, tid, typename Cfg::FA{});
     for (int t = tid; t < ng * nx; t += NT) {
@@ -817,13 +843,13 @@ __global__ __launch_bounds__((mid_threads<N1>())) void k_mid_fast(
     __syncthreads();
     fftr::lds_passes<N1, +1, 1, XB, SS, NT, 1>(buf, tw, tid,
                                                typename fftr::Rev<typename Cfg::FA, RList<>>::type{});
-    cpx<float> v[RF];
-    const cpx<float>* src = buf + s * SS;
-#pragma unroll
-    for (int j = 0; j < RF; ++j) v[j] = src[pad16(i + j * TS)];
-    fftr::pass_twiddle<N1, RF, TS, +1>(v, i, tw);
-    Dft<RF, +1>::run(v);
     if (live) {
+      cpx<float> v[RF];
+      const cpx<float>* src = buf + s * SS;
+#pragma unroll
+      for (int j = 0; j < RF; ++j) v[j] = src[pad16(i + j * TS)];
+      fftr::pass_twiddle<N1, RF, TS, +1>(v, i, tw);
+      Dft<RF, +1>::run(v);
 #pragma unroll
       for (int j = 0; j < RF; ++j) line[i + j * TS] = v[j];
     }
@@ -832,7 +858,7 @@ __global__ __launch_bounds__((mid_threads<N1>())) void k_mid_fast(
 
 // Active list of a group for the persistent schedule: the RVEs of `list`
 // (in list order) that are still iterating, and their count.
-__global__ __launch_bounds__(1024) void k_active_list(const int* __restrict__ list, int nrv,
+static __global__ __launch_bounds__(1024) void k_active_list(const int* __restrict__ list, int nrv,
                                                       const RveState* __restrict__ st, int* __restrict__ alist,
                                                       int* __restrict__ nact) {
   __shared__ int wsum[16];

@@ -686,7 +686,7 @@ struct Decide {
 // count, and after every iteration of the kernels that do not take it
 // themselves.
 constexpr int kConvergeRvesPerBlock = 4;
-__global__ __launch_bounds__(256) void k_converge(const PlanDev* __restrict__ plans,
+static __global__ __launch_bounds__(256) void k_converge(const PlanDev* __restrict__ plans,
                                                   const int* __restrict__ rve_list, int nrve,
                                                   RveState* __restrict__ st, Offs off, Decide dec) {
   const int i = blockIdx.x * kConvergeRvesPerBlock + (int)(threadIdx.x >> 6);
