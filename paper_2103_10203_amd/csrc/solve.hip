@@ -141,7 +141,7 @@ struct Group {
   int* d_alist = nullptr;  // this group's segment of the active list
   bool fast_row = false, fast_col = false;
   bool cp_row = false;   // row passes on the component-parallel kernels throughout
-  bool cp_few = false;   // iteration rows on their form for few workgroups
+  bool cp_few = false;   // iteration rows of a row_fast length on it: few workgroups
   int rb_limit = 1, cb_limit = 1;  // blocks the scratch limit of a no-allocation solve counts
   int rb_iter = 1;       // rows per workgroup of the iteration's row kernel
   bool cp_col = false;   // columns of the lengths outside ColCfg (and FP64)
@@ -889,8 +889,18 @@ mor_status launch_row64(SolveCtx& cx, Group& g, dim3 gr, size_t shm, float* eps,
 // path (64) 27.3 / 29.2 ms, 128 RVEs of 256^2 (2048) 2.01 / 2.04 ms, 256 RVEs
 // (4096) 3.26 / 3.25 ms, eight of 128^3 (8192) 9.15 / 9.02 ms.
 constexpr int64_t kRowDecidesMax = 2048;
+// Most workgroups (of four rows) for which the iteration rows of a row_fast
+// length run on the component-parallel kernel instead.  It has a third of the
+// chain per wavefront and four times the workgroups, but more LDS traffic per
+// row, so it wins while the device has room: row_fast / component-parallel per
+// solve, 256^2 with 1, 4, 8, 16 RVEs (64, 256, 512, 1024 workgroups) 753 / 637,
+// 770 / 682, 801 / 785, 888 / 969 us; 384^2 with 1, 4 (96, 384) 889 / 699,
+// 960 / 887; J2 paths of 512^2 with 1, 4 (128, 512) 9.3 / 7.9, 13.6 / 13.0 ms, of
+// 128^2 with 16 (512) 7.3 / 5.8 ms; 64^2 with 16, 64, 256 (256, 1024, 4096)
+// 484 / 421, 498 / 464, 587 / 704 us.
+constexpr int64_t kCpFewMax = 512;
 bool row_decides(const SolveCtx& cx, const Group& g, int rows) {
-  return (g.cp_row || (g.fast_row && !cx.persist)) && !cx.dft &&
+  return (g.cp_row || g.fast_row) && !cx.persist && !cx.dft &&
          (int64_t)((rows + g.rb_iter - 1) / g.rb_iter) * (int64_t)g.rves.size() <= kRowDecidesMax;
 }
 
@@ -914,7 +924,7 @@ mor_status launch_iter(SolveCtx& cx, Group& g, bool first, bool last) {
   ev_begin(cx, PK_ROW, &a);
   if (cx.dft)
     launch_dft_stage<C, MAT>(cx, g, rows, nlen);
-  else if (g.cp_row || (g.cp_few && !pers)) {
+  else if (g.cp_row || g.cp_few) {
     CpArgs a = cp_args(cx, g);
     if (!first && row_decides(cx, g, rows)) a.dec = dec;
     if (!cp_row(C, nh, cx.fp64, MAT == MAT_J2, CP_ITER, rows, a)) return no_kernel("row");
@@ -1088,6 +1098,17 @@ void choose_row(const SolveCtx& cx, Group& g) {
   const int nlen = g.ndim == 2 ? g.n1 : g.n2;
   const int rows = g.ndim == 2 ? g.n0 : g.n0 * g.n1;
   g.rb_iter = g.rb;
+  // lengths of row_fast: the component-parallel kernel has the factors of the
+  // default variant and stands in for that one only.  Its results differ from
+  // row_fast's by rounding (in registers the compiler merges products of the
+  // law and the transforms that here meet through LDS).
+  const int nh = nlen / 2;
+  if (!g.fast_row || cx.dft || g.rvar != row_default(cx.C, nh, cx.j2)) return;
+  if ((int64_t)cx.C * g.nlast_max * rows * (int64_t)sizeof(cpx<float>) >= (1LL << 31)) return;
+  const int rb = cp_row_rb(cx.C, nh, false, cx.j2);
+  if (rb == 0 || (int64_t)((rows + rb - 1) / rb) * (int64_t)g.rves.size() > kCpFewMax) return;
+  g.cp_few = true;
+  g.rb_iter = rb;
 }
 
 // Prepare the context: plan table, groups, offsets, states.
@@ -1202,6 +1223,9 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
     g.xb = g.ndim == 3 ? cols_per_block(cx.C, g.n1, es) : 1;
     if (!g.fast_row && !g.cp_row && !cx.dft) g.rb = std::min(g.rb, rows);
   }
+  // the iteration's row kernel, by the whole group's size: the sub-batches of
+  // a group run the same one, so that results do not depend on the cut
+  for (auto& g : cx.groups) choose_row(cx, g);
   // Sub-batches: a group's RVEs are cut into runs whose transform lines fit
   // in the device's last-level cache, and the iteration loop runs the chunk
   // of iterations of one sub-batch before the next, so the lines the row
@@ -1242,8 +1266,6 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
     }
     cx.groups.swap(split);
   }
-  // the iteration's row kernel: chosen per sub-batch, by its size
-  for (auto& g : cx.groups) choose_row(cx, g);
   std::vector<int> gof(B);
   for (size_t gi = 0; gi < cx.groups.size(); ++gi)
     for (int b : cx.groups[gi].rves) gof[b] = (int)gi;

@@ -20,7 +20,7 @@ using namespace mor_k;
 
 // Factorisation of a row of length 2 NH: register pass radix RL, inverse LDS
 // passes RA (forward: reversed).  Lengths that row_fast also serves have the
-// factors of its default, so the results are the same bits.
+// factors of its default.
 template <int C, int NH, int MAT>
 struct RowF;
 template <int C, int MAT> struct RowF<C, 12, MAT>  { static constexpr int RL = 3; using RA = RList<4>; };

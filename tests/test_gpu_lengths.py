@@ -1,6 +1,6 @@
 """Compile-time kernels of the 2^a 3^b lengths: every row length with a column
-length, each form of the row kernel (few and many workgroups, which must give
-the same bits), FP32 and FP64, Hooke and J2, 2D and 3D, against the oracle."""
+length, one RVE and many (the same bits where one kernel serves both; within
+rounding on the lengths with a kernel for few workgroups), FP32 and FP64, 2D and 3D, against the oracle."""
 import math
 
 import numpy as np
@@ -47,9 +47,15 @@ def test_2d_few_and_many(n0, n1):
     many = mor.solve(plan, eb, native_phases(), 1e-6, want_fields=True)
     few = mor.solve(plan, eb[:1], native_phases(), 1e-6, want_fields=True)
     _check(mor, g, M, eb[0], few, 0)
-    assert many.iterations[0] == few.iterations[0]
-    assert np.array_equal(many.eff_stress[0], few.eff_stress[0])
-    assert bool((many.strain[0] == few.strain[0]).all())
+    if (n0, n1) in SHARED:
+        # two kernels: FP32 rounding apart (a few 1e-7 of the field after some
+        # 30 iterations), and an iteration where rounding crosses the tolerance
+        assert abs(int(many.iterations[0]) - int(few.iterations[0])) <= 1
+        assert rel_l2(many.strain[0].cpu().numpy(), few.strain[0].cpu().numpy()) < 3e-6
+    else:
+        assert many.iterations[0] == few.iterations[0]
+        assert np.array_equal(many.eff_stress[0], few.eff_stress[0])
+        assert bool((many.strain[0] == few.strain[0]).all())
     if n0 * n1 <= 72 * 72:
         _check(mor, g, M, eb[-1], many, B - 1)
 
@@ -101,5 +107,28 @@ def test_3d(shape):
     many = mor.solve(plan, eb, native_phases(), 1e-6, want_fields=True)
     few = mor.solve(plan, eb[:1], native_phases(), 1e-6, want_fields=True)
     _check(mor, g, M, eb[0], few, 0)
-    assert many.iterations[0] == few.iterations[0]
-    assert bool((many.strain[0] == few.strain[0]).all())
+    if shape[2] in (64, 128):
+        assert rel_l2(many.strain[0].cpu().numpy(), few.strain[0].cpu().numpy()) < 3e-6
+    else:
+        assert many.iterations[0] == few.iterations[0]
+        assert bool((many.strain[0] == few.strain[0]).all())
+
+
+@pytest.mark.parametrize("n0,n1", SHARED + [(64, 64)])
+def test_2d_j2_few_and_many(n0, n1):
+    import paper_2103_10203_amd as mor
+    import torch
+    g = _map((n0, n1), n0 * n1)
+    plan = mor.Plan(g, int(math.ceil(0.06 * g.size)))
+    B = 520 * 4 // n0 + 1  # more than 512 workgroups of four rows
+    d = np.random.default_rng(n1).normal(size=(B, 1, 3))
+    paths = 0.006 * d / np.linalg.norm(d, axis=2, keepdims=True) * np.array([0.5, 1.0])[None, :, None]
+    state = torch.zeros(5 * g.size * B, dtype=torch.float32, device="cuda")
+    many = mor.solve_path_multi([plan], [0] * B, paths, native_phases(j2=True), 1e-6, state)
+    one = torch.zeros(5 * g.size, dtype=torch.float32, device="cuda")
+    few = mor.solve_path(plan, paths[3], native_phases(j2=True), 1e-6, one)
+    # two kernels, both within the FP32 bars of the oracle (1e-5 of sigma_bar,
+    # 1e-4 of the fields), so within twice those of each other
+    assert np.all(np.abs(many.iterations[3] - few.iterations) <= 1)
+    assert np.max(np.abs(many.eff_stress[3][:, :4] - few.eff_stress)) < 2e-5 * np.max(np.abs(few.eff_stress))
+    assert rel_l2(state.view(B, 5, -1)[3, 4].cpu().numpy(), one.view(5, -1)[4].cpu().numpy()) < 2e-4
