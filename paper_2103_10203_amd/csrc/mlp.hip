@@ -24,98 +24,112 @@ namespace {
 
 // ------------------------------------------------------------------ FP32 GEMM
 // C[m][n] = sum_k opA[m][k] opB[k][n], opA[m][k] = TA ? A[k*lda+m] : A[m*lda+k],
-// opB[k][n] = TB ? B[n*ldb+k] : B[k*ldb+n].  64x64 tile, K step 16, 256
-// threads, 4x4 outputs per thread.
+// opB[k][n] = TB ? B[n*ldb+k] : B[k*ldb+n], on the FP32 matrix instructions
+// (FP32 products, FP32 accumulation in the order of k).  Workgroup = four
+// wavefronts on a T x T tile: T = 64 with one 32x32 block (32x32x2) per
+// wavefront, or T = 32 with one 16x16 block (16x16x4), which gives four times
+// the workgroups.  K is never split, so that each output is one chain of k
+// like the sum it is (the same bits as a chain of FMAs), and the small tile
+// fills the chip instead: the training shapes (512 rows, 512 to 4608 columns)
+// have 64 to 576 tiles of 64.  K is staged GK at a time through LDS, the next
+// stage's loads in flight during the products.  Bound by the stages' latency:
+// 512x4608, K = 512 takes 44 us (55 TFLOP/s), 512x512, K = 512 14 us.  A
+// gradient of the 1025-512-512-4608 network on 512 rows takes 0.29 ms; on
+// vector FMAs with 64x64 tiles (and a serial column sum) it took 1.85 ms.
 enum { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_RELU = 2, EPI_RELU_MASK = 3 };
 
-constexpr int GT = 64, GK = 16;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-template <bool TA, bool TB, int EPI>
+template <int EPI>
+__device__ __forceinline__ void gemm_store(float v, int64_t o, int gn, float* __restrict__ C,
+                                           const float* __restrict__ bias, float* __restrict__ Zout,
+                                           const float* __restrict__ Zmask) {
+  if (EPI == EPI_BIAS) v += bias[gn];
+  if (EPI == EPI_BIAS_RELU) {
+    v += bias[gn];
+    Zout[o] = v;
+    v = fmaxf(v, 0.f);
+  }
+  if (EPI == EPI_RELU_MASK) v = Zmask[o] > 0.f ? v : 0.f;
+  C[o] = v;
+}
+
+template <int T, bool TA, bool TB, int EPI>
 __global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, const float* __restrict__ A, int lda,
                                               const float* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
                                               const float* __restrict__ bias, float* __restrict__ Zout,
                                               const float* __restrict__ Zmask) {
-  __shared__ float As[GK][GT + 4];
-  __shared__ float Bs[GK][GT + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-  float acc[4][4] = {};
+  constexpr int W = T / 2;             // block of a wavefront
+  constexpr int GK = T == 64 ? 32 : 64;  // k of a stage
+  constexpr int KI = T == 64 ? 2 : 4;  // k of a matrix instruction
+  // LDS row stride, 33 mod 64 (T = 64) or 17 mod 32 (T = 32): the k rows that
+  // a wavefront reads at once lie on different banks, as do the k of a
+  // transposed store
+  constexpr int LD = T == 64 ? 97 : 49;
+  __shared__ float As[GK][LD];
+  __shared__ float Bs[GK][LD];
+  const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
+  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
+  constexpr int Q = T * GK / 256;  // elements per thread and operand
+  float ra[Q], rb[Q];
+  // (m, k) and (n, k) of a thread's element q: the contiguous index of the
+  // operand runs over the lanes
+  auto ak = [&](int q) { return TA ? tid / T + q * (256 / T) : tid % GK; };
+  auto am = [&](int q) { return TA ? tid % T : tid / GK + q * (256 / GK); };
+  auto bk = [&](int q) { return TB ? tid % GK : tid / T + q * (256 / T); };
+  auto bn = [&](int q) { return TB ? tid / GK + q * (256 / GK) : tid % T; };
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      ra[q] = 0.f;
+      rb[q] = 0.f;
+      if (m0 + am(q) < M && k0 + ak(q) < K)
+        ra[q] = TA ? A[(int64_t)(k0 + ak(q)) * lda + m0 + am(q)] : A[(int64_t)(m0 + am(q)) * lda + k0 + ak(q)];
+      if (n0 + bn(q) < N && k0 + bk(q) < K)
+        rb[q] = TB ? B[(int64_t)(n0 + bn(q)) * ldb + k0 + bk(q)] : B[(int64_t)(k0 + bk(q)) * ldb + n0 + bn(q)];
+    }
+  };
+  f32x16 acc32;
+  f32x4 acc16;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc32[e] = 0.f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc16[e] = 0.f;
+  const int wm = (wave / 2) * W, wn = (wave % 2) * W;
+  const int lr = lane % W, lkk = lane / W;  // lane: row / column lr at k = lkk
+  fetch(0);
   for (int k0 = 0; k0 < K; k0 += GK) {
-    // A tile: 64 (m) x 16 (k)
+    __syncthreads();  // the previous stage has been read
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int t = tid + q * 256;
-      int mm, kk;
-      if (TA) {  // contiguous along m
-        mm = t % GT;
-        kk = t / GT;
-      } else {  // contiguous along k
-        kk = t % GK;
-        mm = t / GK;
-      }
-      const int gm = m0 + mm, gk = k0 + kk;
-      float v = 0.f;
-      if (gm < M && gk < K) v = TA ? A[(int64_t)gk * lda + gm] : A[(int64_t)gm * lda + gk];
-      As[kk][mm] = v;
-    }
-    // B tile: 16 (k) x 64 (n)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int t = tid + q * 256;
-      int kk, nn;
-      if (TB) {  // contiguous along k
-        kk = t % GK;
-        nn = t / GK;
-      } else {  // contiguous along n
-        nn = t % GT;
-        kk = t / GT;
-      }
-      const int gk = k0 + kk, gn = n0 + nn;
-      float v = 0.f;
-      if (gk < K && gn < N) v = TB ? B[(int64_t)gn * ldb + gk] : B[(int64_t)gk * ldb + gn];
-      Bs[kk][nn] = v;
+    for (int q = 0; q < Q; ++q) {
+      As[ak(q)][am(q)] = ra[q];
+      Bs[bk(q)][bn(q)] = rb[q];
     }
     __syncthreads();
+    if (k0 + GK < K) fetch(k0 + GK);
 #pragma unroll
-    for (int kk = 0; kk < GK; ++kk) {
-      float a[4], bb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bb[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], bb[j], acc[i][j]);
+    for (int kk = 0; kk < GK; kk += KI) {
+      const float a = As[kk + lkk][wm + lr], b = Bs[kk + lkk][wn + lr];
+      if constexpr (T == 64) acc32 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc32, 0, 0, 0);
+      else acc16 = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc16, 0, 0, 0);
     }
-    __syncthreads();
   }
+  const int gn = n0 + wn + lr;
+  if (gn >= N) return;
+  // element e of a lane: 32x32 block: row (e / 4) * 8 + (lane / 32) * 4 + e % 4,
+  // column lane % 32; 16x16 block: row (lane / 16) * 4 + e, column lane % 16
+  constexpr int NE = T == 64 ? 16 : 4;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int gm = m0 + ty * 4 + i;
+  for (int e = 0; e < NE; ++e) {
+    const int gm = m0 + wm + (T == 64 ? (e / 4) * 8 + lkk * 4 + e % 4 : lkk * 4 + e);
     if (gm >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int gn = n0 + tx * 4 + j;
-      if (gn >= N) continue;
-      const int64_t o = (int64_t)gm * ldc + gn;
-      float v = acc[i][j];
-      if (EPI == EPI_BIAS) v += bias[gn];
-      if (EPI == EPI_BIAS_RELU) {
-        v += bias[gn];
-        Zout[o] = v;
-        v = fmaxf(v, 0.f);
-      }
-      if (EPI == EPI_RELU_MASK) v = Zmask[o] > 0.f ? v : 0.f;
-      C[o] = v;
-    }
+    gemm_store<EPI>(T == 64 ? acc32[e] : acc16[e & 3], (int64_t)gm * ldc + gn, gn, C, bias, Zout, Zmask);
   }
 }
 
 // ------------------------------------------------------------------ bf16 helpers
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ unsigned short f2bf(float f) {
   // round to nearest even
@@ -265,12 +279,23 @@ __global__ void k_mse(const float* __restrict__ Y, const float* __restrict__ T, 
   if (threadIdx.x == 0) part[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-// db[n] = sum_b dZ[b][n], fixed order in FP64.
-__global__ void k_colsum(const float* __restrict__ dZ, int B, int N, float* __restrict__ db) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
+// db[n] = sum_b dZ[b][n] in FP64, fixed order: 16 threads per column take
+// every 16th row, then their sums in order (5 us for 512 rows; one thread per
+// column is a chain of B dependent additions).
+__global__ __launch_bounds__(1024) void k_colsum(const float* __restrict__ dZ, int B, int N, float* __restrict__ db) {
+  __shared__ double red[16][64];
+  const int c = threadIdx.x % 64, q = threadIdx.x / 64;
+  const int n = blockIdx.x * 64 + c;
   double s = 0.0;
-  for (int b = 0; b < B; ++b) s += dZ[(int64_t)b * N + n];
+  if (n < N) {
+#pragma unroll 8
+    for (int b = q; b < B; b += 16) s += dZ[(int64_t)b * N + n];
+  }
+  red[q][c] = s;
+  __syncthreads();
+  if (q != 0 || n >= N) return;
+#pragma unroll
+  for (int k = 1; k < 16; ++k) s += red[k][c];
   db[n] = (float)s;
 }
 
@@ -484,11 +509,22 @@ struct mor_mlp {
 
 namespace {
 
+// Fewest tiles of 64 (two per CU) for which they are used: below that the
+// small tile's four times as many workgroups fill the chip (512x512, 64 tiles
+// of 64, would leave three of four CUs idle).
+constexpr int64_t kGemmTiles64 = 512;
+
 template <bool TA, bool TB, int EPI>
 void gemm(hipStream_t st, int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
           const float* bias = nullptr, float* Z = nullptr, const float* Zm = nullptr) {
-  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT);
-  k_gemm<TA, TB, EPI><<<grid, 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, bias, Z, Zm);
+  const int64_t t64 = (int64_t)((N + 63) / 64) * ((M + 63) / 64);
+  if (t64 >= kGemmTiles64) {
+    k_gemm<64, TA, TB, EPI><<<dim3((N + 63) / 64, (M + 63) / 64), 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, bias,
+                                                                               Z, Zm);
+  } else {
+    k_gemm<32, TA, TB, EPI><<<dim3((N + 31) / 32, (M + 31) / 32), 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, bias,
+                                                                               Z, Zm);
+  }
 }
 
 mor_status mlp_reserve(mor_mlp* net, int64_t B) {
@@ -497,6 +533,7 @@ mor_status mlp_reserve(mor_mlp* net, int64_t B) {
   (void)hipFree(net->part);
   net->ws = nullptr;
   net->part = nullptr;
+  net->cap_b = 0;
   // Z1 H1 Z2 H2 (B x hid each), Y dY (B x out), dH dZ (B x hid)
   const int64_t n = B * (6 * (int64_t)net->hid + 2 * (int64_t)net->out);
   if (hipMalloc((void**)&net->ws, n * sizeof(float)) != hipSuccess ||
@@ -891,17 +928,17 @@ extern "C" mor_status mor_mlp_grad(mor_mlp_t net, const float* X, const float* T
   const int hid = net->hid, in = net->in, out = net->out, Bi = (int)B;
   // layer 3
   gemm<true, false, EPI_STORE>(st, hid, out, Bi, a.H2, hid, a.dY, out, G + net->off_W3(), out);
-  k_colsum<<<(out + 255) / 256, 256, 0, st>>>(a.dY, Bi, out, G + net->off_b3());
+  k_colsum<<<(out + 63) / 64, 1024, 0, st>>>(a.dY, Bi, out, G + net->off_b3());
   gemm<false, true, EPI_RELU_MASK>(st, Bi, hid, out, a.dY, out, P + net->off_W3(), out, a.dZ, hid, nullptr, nullptr,
                                    a.Z2);
   // layer 2
   gemm<true, false, EPI_STORE>(st, hid, hid, Bi, a.H1, hid, a.dZ, hid, G + net->off_W2(), hid);
-  k_colsum<<<(hid + 255) / 256, 256, 0, st>>>(a.dZ, Bi, hid, G + net->off_b2());
+  k_colsum<<<(hid + 63) / 64, 1024, 0, st>>>(a.dZ, Bi, hid, G + net->off_b2());
   gemm<false, true, EPI_RELU_MASK>(st, Bi, hid, hid, a.dZ, hid, P + net->off_W2(), hid, a.dH, hid, nullptr, nullptr,
                                    a.Z1);
   // layer 1
   gemm<true, false, EPI_STORE>(st, in, hid, Bi, X, in, a.dH, hid, G + net->off_W1(), hid);
-  k_colsum<<<(hid + 255) / 256, 256, 0, st>>>(a.dH, Bi, hid, G + net->off_b1());
+  k_colsum<<<(hid + 63) / 64, 1024, 0, st>>>(a.dH, Bi, hid, G + net->off_b1());
   MOR_LAUNCH_CHECK("mlp backward");
   if (loss) {
     std::vector<double> part(nblk);
