@@ -315,7 +315,9 @@ struct SolveCtx {
   bool noalloc = false;
   unsigned char* arena = nullptr;
   size_t arena_cap = 0, arena_used = 0;
-  unsigned int h_active_local = 0;
+  unsigned int h_active_local[2] = {0, 0};
+  unsigned int chunk_no = 0;  // number of the chunk being launched, 0: its progress is not wanted
+  double rate = 0.0;          // log2 of the residual's fall per iteration, last measured (0: not yet)
   size_t pin_used = 0;       // bytes of the workspace's pinned staging taken by this solve
   bool pin_claimed = false;  // the staging was made ready for this solve
   cpx<double>* yl64() const { return reinterpret_cast<cpx<double>*>(d_yl); }
@@ -432,6 +434,26 @@ mor_status upload(SolveCtx& cx, T* dst, const std::vector<T>& src) {
   MOR_HIP_TRY(hipMemcpyAsync(dst, cx.keep.back().data(), nb, hipMemcpyHostToDevice, cx.st));
   return MOR_OK;
 }
+
+// The small arrays of a solve's setup in one device block, filled by one
+// copy: as seven copies they took 40 us of the 660 us one 256^2 RVE needs.
+// Pieces are 256-byte aligned, as buffers of their own would be.
+struct SetupBlock {
+  std::vector<char> host;  // the uploaded part
+  size_t total = 0;
+  size_t take(size_t bytes) {
+    const size_t o = total;
+    total += (std::max<size_t>(bytes, 1) + 255) / 256 * 256;
+    return o;
+  }
+  template <typename T>
+  size_t add(const std::vector<T>& v) {
+    const size_t o = take(v.size() * sizeof(T));
+    host.resize(o + v.size() * sizeof(T));
+    if (!v.empty()) std::memcpy(host.data() + o, v.data(), v.size() * sizeof(T));
+    return o;
+  }
+};
 
 bool finite(double v) { return std::isfinite(v); }
 
@@ -915,7 +937,7 @@ mor_status launch_iter(SolveCtx& cx, Group& g, bool first, bool last) {
   dim3 gr((rows + g.rb - 1) / g.rb, (unsigned)g.rves.size());
   hipEvent_t a{};
   const bool pers = cx.persist && !cx.dft;
-  const Decide dec{cx.d_part, g.cb, cx.d_active};
+  const Decide dec{cx.d_part, g.cb, cx.d_active, last ? cx.chunk_no : 0u};
   if (pers) {
     // queue of this iteration: the group's still-iterating RVEs
     k_active_list<<<1, 1024, 0, cx.st>>>(g.d_list, (int)g.rves.size(), cx.d_st, g.d_alist, cx.d_nact + g.gidx);
@@ -1147,8 +1169,8 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
   for (size_t i = 0; i < plans.size(); ++i) pd[i] = plans[i]->dev;
   cx.plan_dev.resize(B);
   for (int64_t b = 0; b < B; ++b) cx.plan_dev[b] = plans[plan_of[b]]->dev;
-  if ((s = cx_get(cx, "plans", pd.size(), &cx.d_plans)) != MOR_OK) return s;
-  if ((s = upload(cx, cx.d_plans, pd)) != MOR_OK) return s;
+  SetupBlock blk;
+  const size_t o_plans = blk.add(pd);
   // groups by grid
   std::map<std::vector<int>, int> gidx;
   for (int64_t b = 0; b < B; ++b) {
@@ -1297,14 +1319,7 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
                                    : std::max(nrb, ncb);
     nblk[b] = nrb;
   }
-  int64_t* d_offs;
-  if ((s = cx_get(cx, "offs", offs.size(), &d_offs)) != MOR_OK) return s;
-  if ((s = upload(cx, d_offs, offs)) != MOR_OK) return s;
-  cx.off.yl = d_offs;
-  cx.off.yc = d_offs + B;
-  cx.off.coef = d_offs + 2 * B;
-  cx.off.field = d_offs + 3 * B;
-  cx.off.part = d_offs + 4 * B;
+  const size_t o_offs = blk.add(offs);
   // counts in FP32 complex elements; FP64 complex takes two
   const size_t ew = cx.fp64 ? 2 : 1;
   if ((s = cx_get(cx, "yl", (size_t)yl * ew, &cx.d_yl)) != MOR_OK) return s;
@@ -1316,10 +1331,6 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
   if ((s = cx_get(cx, "coef", (size_t)co * ew, &cx.d_coef)) != MOR_OK) return s;
   if (cx.dft && (s = cx_get(cx, "dfte", (size_t)fo * cx.C, &cx.d_dfte)) != MOR_OK) return s;
   if ((s = get_parts(cx, (size_t)pa, (size_t)pa_limit)) != MOR_OK) return s;
-  if ((s = cx_get(cx, "eff", (size_t)B * cx.S, &cx.d_eff)) != MOR_OK) return s;
-  if ((s = cx_get(cx, "active", 1, &cx.d_active)) != MOR_OK) return s;
-  if ((s = cx_get(cx, "ebar", (size_t)B * cx.C, &cx.d_ebar)) != MOR_OK) return s;
-  if ((s = cx_get(cx, "state", (size_t)B, &cx.d_st)) != MOR_OK) return s;
   // group lists and final block counts (per group position)
   std::vector<int> lists, nblk_list;
   std::vector<size_t> lstart;
@@ -1330,11 +1341,26 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
       nblk_list.push_back(nblk[b]);
     }
   }
-  int* d_lists;
-  if ((s = cx_get(cx, "lists", lists.size(), &d_lists)) != MOR_OK) return s;
-  if ((s = cx_get(cx, "nblk", nblk_list.size(), &cx.d_nblk)) != MOR_OK) return s;
-  if ((s = upload(cx, d_lists, lists)) != MOR_OK) return s;
-  if ((s = upload(cx, cx.d_nblk, nblk_list)) != MOR_OK) return s;
+  const size_t o_lists = blk.add(lists), o_nblk = blk.add(nblk_list);
+  // macro strains, counter and states last, as a load path resets them, then
+  // the effective stresses (not uploaded, read back with the states)
+  const std::vector<double> eb(ebar, ebar + B * cx.C);
+  const std::vector<unsigned int> act = {(unsigned int)B, 0u};
+  const std::vector<RveState> hs = fresh_states(cx, plans, plan_of, ebar, tol, max_iter);
+  const size_t o_ebar = blk.add(eb), o_act = blk.add(act), o_st = blk.add(hs);
+  const size_t o_eff = blk.take((size_t)B * cx.S * sizeof(double));
+  unsigned char* base;
+  if ((s = cx_get(cx, "setup", blk.total, &base)) != MOR_OK) return s;
+  if ((s = upload(cx, (char*)base, blk.host)) != MOR_OK) return s;
+  cx.d_plans = (PlanDev*)(base + o_plans);
+  const int64_t* d_offs = (const int64_t*)(base + o_offs);
+  cx.off = Offs{d_offs, d_offs + B, d_offs + 2 * B, d_offs + 3 * B, d_offs + 4 * B};
+  int* d_lists = (int*)(base + o_lists);
+  cx.d_nblk = (int*)(base + o_nblk);
+  cx.d_ebar = (double*)(base + o_ebar);
+  cx.d_active = (unsigned int*)(base + o_act);
+  cx.d_st = (RveState*)(base + o_st);
+  cx.d_eff = (double*)(base + o_eff);
   for (size_t gi = 0; gi < cx.groups.size(); ++gi) cx.groups[gi].d_list = d_lists + lstart[gi];
   if (cx.persist) {
     if ((s = cx_get(cx, "alist", lists.size(), &cx.d_alist)) != MOR_OK) return s;
@@ -1346,13 +1372,6 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
   }
   // nblk is indexed by group position in k_sig_reduce: shift per group
   // (k_sig_reduce receives the group's list; its nblk pointer is offset below)
-  // states
-  std::vector<RveState> hs = fresh_states(cx, plans, plan_of, ebar, tol, max_iter);
-  std::vector<double> eb(ebar, ebar + B * cx.C);
-  if ((s = upload(cx, cx.d_st, hs)) != MOR_OK) return s;
-  if ((s = upload(cx, cx.d_ebar, eb)) != MOR_OK) return s;
-  std::vector<unsigned int> act(1, (unsigned int)B);
-  if ((s = upload(cx, cx.d_active, act)) != MOR_OK) return s;
   // J2 state
   if (cx.j2) {
     if (jstate_user) {
@@ -1404,7 +1423,11 @@ struct GraphChunk {
   }
 };
 
-mor_status run(SolveCtx& cx, const cpx<float>* warm, const mor_solve_opts* opts, float* eps, float* sig) {
+// Longest adaptive chunk, and the chunk numbers that fit the progress word.
+constexpr int kChunkMax = 64;
+constexpr unsigned int kChunksCounted = (1u << (32 - kProgBits)) - 2;
+
+mor_status run(SolveCtx& cx, const cpx<float>* warm, const mor_solve_opts* opts, double tol, float* eps, float* sig) {
   mor_status s;
   if (warm) {
     // an RVE whose warm coefficients hold a NaN/Inf starts cold instead
@@ -1428,25 +1451,44 @@ mor_status run(SolveCtx& cx, const cpx<float>* warm, const mor_solve_opts* opts,
   // a chunk has the same arguments (the iteration state lives in device
   // memory), so the replays are the eager sequence.
   GraphChunk gc;
+  cx.chunk_no = 0;
   if (opts && opts->use_graph) {
     if ((s = gc.record(cx, check)) != MOR_OK) return s;
   }
-  while (true) {
+  // The default interval adapts: a chunk ends where the slowest RVE is
+  // expected to stop, from how fast its residual has fallen, so that a solve
+  // looks at the counter two or three times (each look stalls the stream for
+  // 15-25 us) and launches few iterations that find nothing to do (4-10 us
+  // each).  When an RVE stops is decided on the device either way.
+  const bool adapt = !gc.exec && !(opts && opts->check_every > 0);
+  int len = check;
+  double prev = -1.0;  // margin log2(r / tol) at the last look
+  for (unsigned int chunk = 1;; ++chunk) {
+    cx.chunk_no = adapt && chunk <= kChunksCounted ? chunk : 0;
     if (gc.exec) {
       MOR_HIP_TRY(hipGraphLaunch(gc.exec, cx.st));
     } else {
       // sub-batch outermost: its lines stay cached across its iterations
       for (auto& g : cx.groups)
-        if ((s = do_chunk(cx, g, check)) != MOR_OK) return s;
+        if ((s = do_chunk(cx, g, len)) != MOR_OK) return s;
     }
-    done += check;
-    unsigned int* hact = cx.noalloc ? &cx.h_active_local : cx.ws->h_active;
-    MOR_HIP_TRY(hipMemcpyAsync(hact, cx.d_active, sizeof(unsigned int), hipMemcpyDeviceToHost, cx.st));
+    done += len;
+    unsigned int* hact = cx.noalloc ? cx.h_active_local : cx.ws->h_active;
+    MOR_HIP_TRY(hipMemcpyAsync(hact, cx.d_active, 2 * sizeof(unsigned int), hipMemcpyDeviceToHost, cx.st));
     MOR_HIP_TRY(hipStreamSynchronize(cx.st));
-    if (*hact == 0u) break;
-    if (done > max_iter + check) {
+    if (hact[0] == 0u) break;
+    if (done > max_iter + len) {
       mor_set_error("iteration loop did not drain");
       return MOR_E_DEVICE;
+    }
+    if (cx.chunk_no) {  // past the counted chunks (a million iterations) the last length stays
+      const double m = (double)(hact[1] & ((1u << kProgBits) - 1)) / kProgUnit;
+      // before a second look the fall is taken from a first residual of 1/4
+      const double fall = prev >= 0.0 ? (prev - m) / len : (std::log2(0.25 / tol) - m) / len;
+      if (fall > 0.0 && (prev >= 0.0 || cx.rate == 0.0)) cx.rate = fall;
+      prev = m;
+      const double left = cx.rate > 0.0 ? std::ceil(m / cx.rate) : check;
+      len = (int)std::min(std::max(left, 2.0), (double)kChunkMax);
     }
   }
   // finalize; the nblk pointer is offset per group
@@ -1478,14 +1520,16 @@ mor_status collect(SolveCtx& cx, mor_outputs* out, int eff_stride, std::vector<R
   std::vector<RveState> hs(cx.B);
   std::vector<double> eff((size_t)cx.B * cx.S);
   const size_t hs_nb = hs.size() * sizeof(RveState), eff_nb = eff.size() * sizeof(double);
-  unsigned char* hs_pin = pin_slot(cx, hs_nb);
-  unsigned char* eff_pin = (out && out->eff_stress) ? pin_slot(cx, eff_nb) : nullptr;
-  MOR_HIP_TRY(hipMemcpyAsync(hs_pin ? (void*)hs_pin : (void*)hs.data(), cx.d_st, hs_nb, hipMemcpyDeviceToHost,
-                             cx.st));
-  if (out && out->eff_stress)
-    MOR_HIP_TRY(hipMemcpyAsync(eff_pin ? (void*)eff_pin : (void*)eff.data(), cx.d_eff, eff_nb,
-                               hipMemcpyDeviceToHost, cx.st));
-  if (hs_pin || eff_pin) {
+  // states and effective stresses are neighbours in the setup block: one copy
+  const bool want_eff = out && out->eff_stress;
+  const size_t eff_at = (size_t)((unsigned char*)cx.d_eff - (unsigned char*)cx.d_st);
+  const size_t nb = want_eff ? eff_at + eff_nb : hs_nb;
+  unsigned char* pin = pin_slot(cx, nb);
+  std::vector<unsigned char> pageable;
+  if (!pin) pageable.resize(nb);
+  unsigned char* back = pin ? pin : pageable.data();
+  MOR_HIP_TRY(hipMemcpyAsync(back, cx.d_st, nb, hipMemcpyDeviceToHost, cx.st));
+  if (pin) {
     mor_status ms = pin_mark(cx);
     if (ms != MOR_OK) return ms;
   }
@@ -1503,8 +1547,8 @@ mor_status collect(SolveCtx& cx, mor_outputs* out, int eff_stride, std::vector<R
   }
   MOR_HIP_TRY(hipStreamSynchronize(cx.st));
   if (cx.ws) cx.ws->pin_busy = false;
-  if (hs_pin) std::memcpy(hs.data(), hs_pin, hs_nb);
-  if (eff_pin) std::memcpy(eff.data(), eff_pin, eff_nb);
+  std::memcpy(hs.data(), back, hs_nb);
+  if (want_eff) std::memcpy(eff.data(), back + eff_at, eff_nb);
   account(cx, hs);
   mor_status worst = MOR_OK;
   for (int64_t b = 0; b < cx.B; ++b) {
@@ -1649,7 +1693,7 @@ mor_status solve_impl(const std::vector<mor_plan*>& plans, const std::vector<int
   }
   cx.want_eps = out && out->strain;
   cx.want_sig = out && out->stress;
-  s = run(cx, opts ? (const cpx<float>*)opts->warm_start : nullptr, opts, out ? out->strain : nullptr,
+  s = run(cx, opts ? (const cpx<float>*)opts->warm_start : nullptr, opts, tol, out ? out->strain : nullptr,
           out ? out->stress : nullptr);
   if (s != MOR_OK) {
     (void)hipStreamSynchronize(cx.st);
@@ -1894,16 +1938,19 @@ mor_status path_impl(const std::vector<mor_plan*>& plans, const std::vector<int>
     const bool last = n == steps - 1;
     if (n > 0) {
       step_ebar(n);
-      if ((s = upload(cx, cx.d_ebar, eb)) != MOR_OK) return s;
-      if ((s = upload(cx, cx.d_st, fresh_states(cx, plans, plan_of, eb.data(), tol, max_iter))) != MOR_OK) return s;
-      if ((s = upload(cx, cx.d_active, std::vector<unsigned int>(1, (unsigned int)B))) != MOR_OK) return s;
+      // macro strains, counter and states: the same pieces as in setup()
+      SetupBlock blk;
+      blk.add(eb);
+      blk.add(std::vector<unsigned int>{(unsigned int)B, 0u});
+      blk.add(fresh_states(cx, plans, plan_of, eb.data(), tol, max_iter));
+      if ((s = upload(cx, (char*)cx.d_ebar, blk.host)) != MOR_OK) return s;
     }
     cx.want_eps = last && eps;
     cx.want_sig = last && sig;
     // step 0 starts from the caller's warm start (or cold), later steps from
     // the previous step's coefficients, read and rewritten in place
     const cpx<float>* warm = n == 0 ? (opts ? (const cpx<float>*)opts->warm_start : nullptr) : cx.d_coef;
-    if ((s = run(cx, warm, opts, last ? eps : nullptr, last ? sig : nullptr)) != MOR_OK) {
+    if ((s = run(cx, warm, opts, tol, last ? eps : nullptr, last ? sig : nullptr)) != MOR_OK) {
       (void)hipStreamSynchronize(cx.st);
       return s;
     }

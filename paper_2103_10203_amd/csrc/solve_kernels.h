@@ -674,11 +674,16 @@ __device__ __forceinline__ void stop_rve(RveState& S, int status, double r, unsi
 
 // What a row kernel needs to take the stop decision of the iteration before
 // it: the column blocks' partial sums, the columns per block, the counter of
-// iterating RVEs.  part = nullptr: the decision has been taken.
+// iterating RVEs (active[0]).  part = nullptr: the decision has been taken.
+// active[1] tells the host how far the slowest RVE is: k_converge raises it to
+// (chunk << kProgBits) | log2(residual / tolerance) in 1/kProgUnit, so that a
+// later chunk's value replaces an earlier one's.
+constexpr int kProgBits = 18, kProgUnit = 1024;
 struct Decide {
   const double* part;
   int cb;
   unsigned int* active;
+  unsigned int chunk;
 };
 
 // The stop decision as a launch of its own (one wavefront per RVE, 4 per
@@ -702,6 +707,12 @@ static __global__ __launch_bounds__(256) void k_converge(const PlanDev* __restri
   double r = 0.0;
   const int end = stop_rule(S, sum, &r);
   stop_rve(S, end, r, dec.active);
+  if (end < 0 && dec.chunk) {
+    const double t = S.tol * S.denom;
+    const float m = 0.5f * log2f((float)(sum / (t * t)));  // at least 0: r >= tol
+    const unsigned int q = (unsigned int)fminf(fmaxf(m, 0.f) * kProgUnit, (float)((1 << kProgBits) - 1));
+    atomicMax(dec.active + 1, (dec.chunk << kProgBits) | q);
+  }
 }
 
 // Per-RVE grid mean of the stress: FP64 sum of the block partials divided by
