@@ -468,8 +468,10 @@ mor_status mor_tune_set(int32_t kernel, int32_t ndim, int32_t length, int32_t va
  * fewest runs of about equal size whose transform lines fit `bytes`, but
  * into no runs of fewer than `min_rves` RVEs, and the iteration loop runs
  * each run's chunk of iterations before the next, so the lines stay in the
- * last-level cache between the row and column passes.  Results do not
- * depend on the cut (every RVE iterates on its own).  Defaults: 192 MiB
+ * last-level cache between the row and column passes.  Large enough runs
+ * are halved and iterate two at a time, on the solve's stream and one of the
+ * library's (joined to it before the call returns), within the same bytes.
+ * Results do not depend on the cut (every RVE iterates on its own).  Defaults: 192 MiB
  * (MOR_SUBBATCH_MIB in the environment, in MiB, sets the start value) and
  * 128 RVEs; bytes = 0 keeps each grid's RVEs together; -1 keeps a value.
  * *prev_bytes, *prev_min (may be NULL) receive the values before the call.

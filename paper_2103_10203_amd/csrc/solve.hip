@@ -171,6 +171,7 @@ struct Group {
   int rb_iter = 1;       // rows per workgroup of the iteration's row kernel
   bool cp_col = false;   // columns of the lengths outside ColCfg (and FP64)
   int* d_list = nullptr;
+  int lane = 0;          // stream its chunks run on (0: the solve's own)
 };
 
 // Size-specialised kernels available for (C, half row length) and (C, n0).
@@ -341,7 +342,6 @@ struct SolveCtx {
   unsigned char* arena = nullptr;
   size_t arena_cap = 0, arena_used = 0;
   unsigned int h_active_local[2] = {0, 0};
-  int64_t line_bytes = 0;     // transform lines of all RVEs
   unsigned int chunk_no = 0;  // number of the chunk being launched, 0: its progress is not wanted
   double rate = 0.0;          // log2 of the residual's fall per iteration, last measured (0: not yet)
   size_t pin_used = 0;       // bytes of the workspace's pinned staging taken by this solve
@@ -1159,6 +1159,28 @@ void choose_row(const SolveCtx& cx, Group& g) {
   g.rb_iter = rb;
 }
 
+// Lanes: sub-batches have nothing to do with each other, so some run their
+// chunks on streams of their own, forked from and joined to the solve's stream
+// around every chunk.
+//  * Several grids: a grid whose launches do not fill the device leaves CUs
+//    idle, so grids run side by side, while the transform lines of all of them
+//    fit the 256 MB Infinity Cache (beyond that they drive each other out): in
+//    turn / side by side, 16 RVEs each of 96x144, 162x108, 288x192 (12 MB)
+//    1976 / 1168 us, of 128^2, 256^2, 384^2 64 each (80 MB) 4.36 / 3.32 ms, 512
+//    each (630 MB) 24.2 / 24.7 ms.
+//  * Otherwise two at a time, each within half the sub-batch limit, so that
+//    one's row pass (bound by VALU issue) overlaps the other's column pass
+//    (bound by latency), if each has at least kPairWgs row workgroups and
+//    kPairBytes of lines; one at a time / in pairs: 1024 RVEs of 256^2 13.1 / 12.2
+//    ms, 1536 of 128^2, 256^2, 384^2 23.7 / 22.3 ms, 16 of 128^3 17.8 / 16.2 ms,
+//    128 of 256^2 (1024 workgroups, 22 MB each) 1.95 / 1.76 ms, but 64 of them
+//    (512) 1.32 / 1.31, four of 48x72x96 (864) 1.69 / 1.76, and 512 of 64^2 (1024,
+//    but 5 MB each) 0.73 / 0.77 ms.
+constexpr int kLanes = 4;  // streams, the solve's own among them
+constexpr size_t kLanesBytes = (size_t)256 << 20;
+constexpr int64_t kPairWgs = 1024;
+constexpr size_t kPairBytes = (size_t)6 << 20;
+
 // Prepare the context: plan table, groups, offsets, states.
 mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::vector<int>& plan_of,
                  const double* ebar, int64_t B, const mor_phase* phase, double tol, const mor_solve_opts* opts,
@@ -1282,22 +1304,41 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
   {
     const size_t limit = subbatch_bytes();
     const size_t es = cx.fp64 ? sizeof(cpx<double>) : sizeof(cpx<float>);
+    auto line_bytes = [&](int b) {
+      const mor_plan* p = plans[plan_of[b]];
+      size_t y = (size_t)cx.C * p->dev.nlast * p->dev.rows * es;
+      if (cx.ndim == 3) y += (size_t)cx.C * p->dev.ncol * p->n[0] * es;
+      return y;
+    };
+    size_t all = 0;
+    for (int64_t b = 0; b < B; ++b) all += line_bytes((int)b);
+    // grids side by side while all lines fit the cache, else (and for one
+    // grid) pairs of sub-batches side by side
+    const bool lanes = !cx.noalloc && !g_prof_on && !(opts && opts->use_graph);
+    const bool side = lanes && cx.groups.size() > 1 && all <= kLanesBytes;
+    const bool pairs = lanes && !side && limit > 0;
     std::vector<Group> split;
     for (const Group& g : cx.groups) {
       std::vector<size_t> yb(g.rves.size());
       size_t total = 0;
       for (size_t q = 0; q < g.rves.size(); ++q) {
-        const mor_plan* p = plans[plan_of[g.rves[q]]];
-        yb[q] = (size_t)cx.C * p->dev.nlast * p->dev.rows * es;
-        if (cx.ndim == 3) yb[q] += (size_t)cx.C * p->dev.ncol * p->n[0] * es;
+        yb[q] = line_bytes(g.rves[q]);
         total += yb[q];
       }
       // as few sub-batches as the limit allows, of about equal size (cut
       // where the running sum passes the next multiple of total / parts)
       const size_t minr = (size_t)std::max<int64_t>(1, subbatch_min_rves().load());
-      const size_t parts = limit > 0 ? std::max<size_t>(1, std::min((total + limit - 1) / limit,
-                                                                    g.rves.size() / minr))
-                                     : 1;
+      size_t parts = limit > 0 ? std::max<size_t>(1, std::min((total + limit - 1) / limit, g.rves.size() / minr)) : 1;
+      if (pairs) {
+        // two at a time: each within half the limit, an even number of them,
+        // unless that leaves too few row workgroups to one
+        const int rows = g.ndim == 2 ? g.n0 : g.n0 * g.n1;
+        const int64_t wgs = (int64_t)((rows + g.rb_iter - 1) / g.rb_iter) * (int64_t)g.rves.size();
+        const size_t want = std::max<size_t>((2 * total + limit - 1) / limit, 1);
+        const size_t p2 = std::min({(want + 1) / 2 * 2, (size_t)(wgs / kPairWgs) / 2 * 2, total / kPairBytes / 2 * 2,
+                                    g.rves.size() / 2 * 2});
+        if (p2 >= 2) parts = p2;
+      }
       Group cur = g;
       cur.rves.clear();
       size_t run = 0, cut = 1;
@@ -1311,6 +1352,20 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
         run += yb[q];
       }
       split.push_back(cur);
+    }
+    if (pairs) {
+      // the sub-batches to the lane with fewer bytes so far, in order
+      size_t sum[2] = {0, 0};
+      for (Group& g : split) {
+        size_t bytes = 0;
+        for (int b : g.rves) bytes += line_bytes(b);
+        g.lane = sum[1] < sum[0] ? 1 : 0;
+        sum[g.lane] += bytes;
+      }
+    } else if (side) {
+      // grid k, in order of appearance, on lane k mod kLanes
+      std::map<std::vector<int>, int> seen;
+      for (Group& g : split) g.lane = seen.emplace(std::vector<int>{g.n0, g.n1, g.n2}, (int)seen.size()).first->second % kLanes;
     }
     cx.groups.swap(split);
   }
@@ -1348,7 +1403,6 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
   const size_t o_offs = blk.add(offs);
   // counts in FP32 complex elements; FP64 complex takes two
   const size_t ew = cx.fp64 ? 2 : 1;
-  cx.line_bytes = (yl + yc) * (int64_t)(ew * sizeof(cpx<float>));
   if ((s = cx_get(cx, "yl", (size_t)yl * ew, &cx.d_yl)) != MOR_OK) return s;
   if (cx.ndim == 3) {
     if ((s = cx_get(cx, "yc", (size_t)yc * ew, &cx.d_yc)) != MOR_OK) return s;
@@ -1450,33 +1504,16 @@ struct GraphChunk {
   }
 };
 
-// Side by side: the grids of a solve have nothing to do with each other, and
-// one whose launches do not fill the device leaves CUs idle, so they run their
-// chunks on streams of their own, forked from and joined to the solve's
-// stream.  While the transform lines of all of them fit the 256 MB Infinity
-// Cache that gains, beyond it they drive each other out: in turn / side by
-// side, 16 RVEs each of 96x144, 162x108, 288x192 (12 MB) 1976 / 1168 us, of
-// 128^2, 256^2, 384^2 64 RVEs each (80 MB) 4.36 / 3.32 ms, 512 each (630 MB)
-// 24.2 / 24.7 ms, 128 each of 512^2 and 384^2 (280 MB) 10.7 / 10.9 ms.
-constexpr size_t kLanes = 4;  // streams, the solve's own among them
-constexpr int64_t kLanesBytes = (int64_t)256 << 20;
-
-// The groups of each stream: grid k (in order of appearance) on stream
-// k mod kLanes, its sub-batches one after the other.  One lane: nothing to
-// run side by side, or no streams (a no-allocation solve has no workspace, a
-// captured chunk one stream, and event times are of one stream's launches).
-std::vector<std::vector<Group*>> lanes_of(SolveCtx& cx, bool single) {
-  std::vector<std::vector<Group*>> lanes;
-  std::vector<const Group*> grids;
+// The groups of each lane (Group::lane); one lane if there are no streams.
+std::vector<std::vector<Group*>> lanes_of(SolveCtx& cx) {
+  std::vector<std::vector<Group*>> lanes(1);
   for (Group& g : cx.groups) {
-    size_t k = 0;
-    while (k < grids.size() &&
-           (grids[k]->n0 != g.n0 || grids[k]->n1 != g.n1 || grids[k]->n2 != g.n2))
-      ++k;
-    if (k == grids.size()) grids.push_back(&g);
-    const size_t lane = single ? 0 : k % kLanes;
-    if (lanes.size() <= lane) lanes.resize(lane + 1);
-    lanes[lane].push_back(&g);
+    if (lanes.size() <= (size_t)g.lane) lanes.resize(g.lane + 1);
+    lanes[g.lane].push_back(&g);
+  }
+  if (lanes.size() > 1 && !cx.ws->side_streams(lanes.size() - 1)) {
+    lanes.assign(1, {});
+    for (Group& g : cx.groups) lanes[0].push_back(&g);
   }
   return lanes;
 }
@@ -1554,8 +1591,7 @@ mor_status run(SolveCtx& cx, const cpx<float>* warm, const mor_solve_opts* opts,
   // 15-25 us) and launches few iterations that find nothing to do (4-10 us
   // each).  When an RVE stops is decided on the device either way.
   const bool adapt = !gc.exec && !(opts && opts->check_every > 0);
-  auto lanes = lanes_of(cx, gc.exec || cx.noalloc || g_prof_on || cx.line_bytes > kLanesBytes);
-  if (lanes.size() > 1 && !cx.ws->side_streams(lanes.size() - 1)) lanes = lanes_of(cx, true);
+  const auto lanes = lanes_of(cx);
   int len = check;
   double prev = -1.0;  // margin log2(r / tol) at the last look
   for (unsigned int chunk = 1;; ++chunk) {

@@ -45,6 +45,26 @@ def test_grids_side_by_side_equal_one_by_one(shapes, prec, other_stream):
             at += n
 
 
+@pytest.mark.parametrize("n,B", [(128, 256), (64, 1030)])
+def test_pairs_equal_one_run(n, B):
+    """Batches that iterate as pairs of runs against one run (limit off): the
+    same bits; just at the rule's line and beyond it, fields included."""
+    import paper_2103_10203_amd as mor
+    g = synth.rsa_fibres(n, n, n / 32, n / 16, seed=n, target_vf=0.35).g
+    plan = mor.Plan(g, int(math.ceil(0.05 * g.size)))
+    eb = synth.macro_strains(B, 3, 5e-3, seed=8)
+    pairs = mor.solve(plan, eb, native_phases(), 1e-6, want_fields=True)
+    keep = mor.tune_subbatch(nbytes=0)
+    try:
+        one = mor.solve(plan, eb, native_phases(), 1e-6, want_fields=True)
+    finally:
+        mor.tune_subbatch(*keep)
+    assert np.array_equal(pairs.iterations, one.iterations)
+    assert np.array_equal(pairs.residual, one.residual)
+    assert np.array_equal(pairs.eff_stress, one.eff_stress)
+    assert bool((pairs.strain == one.strain).all()) and bool((pairs.stress == one.stress).all())
+
+
 def test_paths_side_by_side_equal_one_by_one():
     import paper_2103_10203_amd as mor
     import torch
