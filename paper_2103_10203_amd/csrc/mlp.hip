@@ -16,6 +16,7 @@
 #include <mutex>
 #include <random>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "mor_internal.h"
@@ -33,9 +34,10 @@ namespace {
 // fills the chip instead: the training shapes (512 rows, 512 to 4608 columns)
 // have 64 to 576 tiles of 64.  K is staged GK at a time through LDS, the next
 // stage's loads in flight during the products.  Bound by the stages' latency:
-// 512x4608, K = 512 takes 44 us (55 TFLOP/s), 512x512, K = 512 14 us.  A
-// gradient of the 1025-512-512-4608 network on 512 rows takes 0.29 ms; on
-// vector FMAs with 64x64 tiles (and a serial column sum) it took 1.85 ms.
+// 512x4608, K = 512 takes 35 us (69 TFLOP/s; 44 us staged by single elements),
+// 512x512, K = 512 8 us; stages twice as long measured the same.  A gradient
+// of the 1025-512-512-4608 network on 512 rows takes 0.24 ms; on vector FMAs
+// with 64x64 tiles (and a serial column sum) it took 1.85 ms.
 enum { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_RELU = 2, EPI_RELU_MASK = 3 };
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -55,7 +57,7 @@ __device__ __forceinline__ void gemm_store(float v, int64_t o, int gn, float* __
   C[o] = v;
 }
 
-template <int T, bool TA, bool TB, int EPI>
+template <int T, bool TA, bool TB, int EPI, bool VA, bool VB>
 __global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, const float* __restrict__ A, int lda,
                                               const float* __restrict__ B, int ldb, float* __restrict__ C, int ldc,
                                               const float* __restrict__ bias, float* __restrict__ Zout,
@@ -71,23 +73,43 @@ __global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, const float* 
   __shared__ float Bs[GK][LD];
   const int tid = threadIdx.x, wave = tid / 64, lane = tid % 64;
   const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-  constexpr int Q = T * GK / 256;  // elements per thread and operand
-  float ra[Q], rb[Q];
-  // (m, k) and (n, k) of a thread's element q: the contiguous index of the
-  // operand runs over the lanes
-  auto ak = [&](int q) { return TA ? tid / T + q * (256 / T) : tid % GK; };
-  auto am = [&](int q) { return TA ? tid % T : tid / GK + q * (256 / GK); };
-  auto bk = [&](int q) { return TB ? tid % GK : tid / T + q * (256 / T); };
-  auto bn = [&](int q) { return TB ? tid / GK + q * (256 / GK) : tid % T; };
+  // Staging: an operand's contiguous index runs over the lanes, one element
+  // or (VA, VB) one aligned vector of four at a time: with single elements the
+  // addresses and bounds of a stage cost as many issue slots as its products.
+  constexpr int EA = VA ? 4 : 1, EB = VB ? 4 : 1;
+  constexpr int QA = T * GK / 256 / EA, QB = T * GK / 256 / EB;
+  float ra[QA][EA], rb[QB][EB];
+  constexpr int CA = (TA ? T : GK) / EA, CB = (TB ? GK : T) / EB;  // lanes along the contiguous index
+  auto a1 = [&](int) { return tid % CA * EA; };                    // contiguous index, other index
+  auto a2 = [&](int q) { return tid / CA + q * (256 / CA); };
+  auto b1 = [&](int) { return tid % CB * EB; };
+  auto b2 = [&](int q) { return tid / CB + q * (256 / CB); };
   auto fetch = [&](int k0) {
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      ra[q] = 0.f;
-      rb[q] = 0.f;
-      if (m0 + am(q) < M && k0 + ak(q) < K)
-        ra[q] = TA ? A[(int64_t)(k0 + ak(q)) * lda + m0 + am(q)] : A[(int64_t)(m0 + am(q)) * lda + k0 + ak(q)];
-      if (n0 + bn(q) < N && k0 + bk(q) < K)
-        rb[q] = TB ? B[(int64_t)(n0 + bn(q)) * ldb + k0 + bk(q)] : B[(int64_t)(k0 + bk(q)) * ldb + n0 + bn(q)];
+    for (int q = 0; q < QA; ++q) {
+      const int m = m0 + (TA ? a1(q) : a2(q)), k = k0 + (TA ? a2(q) : a1(q));
+      const float* p = A + (TA ? (int64_t)k * lda + m : (int64_t)m * lda + k);
+      const bool in = m < M && k < K;  // a vector lies wholly inside or outside
+      if constexpr (VA) {
+        float4 v = {0.f, 0.f, 0.f, 0.f};
+        if (in) v = *reinterpret_cast<const float4*>(p);
+        ra[q][0] = v.x; ra[q][1] = v.y; ra[q][2] = v.z; ra[q][3] = v.w;
+      } else {
+        ra[q][0] = in ? *p : 0.f;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < QB; ++q) {
+      const int n = n0 + (TB ? b2(q) : b1(q)), k = k0 + (TB ? b1(q) : b2(q));
+      const float* p = B + (TB ? (int64_t)n * ldb + k : (int64_t)k * ldb + n);
+      const bool in = n < N && k < K;
+      if constexpr (VB) {
+        float4 v = {0.f, 0.f, 0.f, 0.f};
+        if (in) v = *reinterpret_cast<const float4*>(p);
+        rb[q][0] = v.x; rb[q][1] = v.y; rb[q][2] = v.z; rb[q][3] = v.w;
+      } else {
+        rb[q][0] = in ? *p : 0.f;
+      }
     }
   };
   f32x16 acc32;
@@ -102,10 +124,13 @@ __global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, const float* 
   for (int k0 = 0; k0 < K; k0 += GK) {
     __syncthreads();  // the previous stage has been read
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      As[ak(q)][am(q)] = ra[q];
-      Bs[bk(q)][bn(q)] = rb[q];
-    }
+    for (int q = 0; q < QA; ++q)
+#pragma unroll
+      for (int e = 0; e < EA; ++e) As[TA ? a2(q) : a1(q) + e][TA ? a1(q) + e : a2(q)] = ra[q][e];
+#pragma unroll
+    for (int q = 0; q < QB; ++q)
+#pragma unroll
+      for (int e = 0; e < EB; ++e) Bs[TB ? b1(q) + e : b2(q)][TB ? b2(q) : b1(q) + e] = rb[q][e];
     __syncthreads();
     if (k0 + GK < K) fetch(k0 + GK);
 #pragma unroll
@@ -518,13 +543,23 @@ template <bool TA, bool TB, int EPI>
 void gemm(hipStream_t st, int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
           const float* bias = nullptr, float* Z = nullptr, const float* Zm = nullptr) {
   const int64_t t64 = (int64_t)((N + 63) / 64) * ((M + 63) / 64);
-  if (t64 >= kGemmTiles64) {
-    k_gemm<64, TA, TB, EPI><<<dim3((N + 63) / 64, (M + 63) / 64), 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, bias,
-                                                                               Z, Zm);
-  } else {
-    k_gemm<32, TA, TB, EPI><<<dim3((N + 31) / 32, (M + 31) / 32), 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, bias,
-                                                                               Z, Zm);
-  }
+  // vectors of four where the contiguous index, the row stride and the base
+  // are multiples of them
+  auto vec = [](const float* p, int ld, int n) { return ((uintptr_t)p & 15) == 0 && ld % 4 == 0 && n % 4 == 0; };
+  const bool va = vec(A, lda, TA ? M : K), vb = vec(B, ldb, TB ? K : N);
+  auto go = [&](auto t, auto a4, auto b4) {
+    constexpr int T = decltype(t)::value;
+    k_gemm<T, TA, TB, EPI, decltype(a4)::value, decltype(b4)::value>
+        <<<dim3((N + T - 1) / T, (M + T - 1) / T), 256, 0, st>>>(M, N, K, A, lda, B, ldb, C, ldc, bias, Z, Zm);
+  };
+  auto tile = [&](auto t) {
+    if (va && vb) go(t, std::true_type{}, std::true_type{});
+    else if (va) go(t, std::true_type{}, std::false_type{});
+    else if (vb) go(t, std::false_type{}, std::true_type{});
+    else go(t, std::false_type{}, std::false_type{});
+  };
+  if (t64 >= kGemmTiles64) tile(std::integral_constant<int, 64>{});
+  else tile(std::integral_constant<int, 32>{});
 }
 
 mor_status mlp_reserve(mor_mlp* net, int64_t B) {
