@@ -351,23 +351,62 @@ __global__ __launch_bounds__(256) void k_rep_counts(Dims d, int64_t N, int* __re
   }
 }
 
+// A selected pair (or self-conjugate frequency) of rank `rank` whose first
+// member takes place `pos` of the selection: whole pairs are taken until M
+// are reached.  Also records, for every selected frequency, its pair index in
+// rank order (bit 30 set for the partner of the pair's representative);
+// Mact[1] = number of selected pairs.
+__device__ __forceinline__ void take_pair(const Dims& d, int64_t idx, int rank, int64_t pos, bool self, int64_t M,
+                                          int64_t* __restrict__ rank_idx, uint8_t* __restrict__ mask,
+                                          int* __restrict__ pairof, int64_t* __restrict__ Mact) {
+  if (pos >= M) return;
+  rank_idx[pos] = idx;
+  mask[idx] = 1;
+  pairof[idx] = rank;
+  if (!self) {
+    int k[3], c[3];
+    unravel(d, idx, k);
+    conj_k(d, k, c);
+    const int64_t pidx = ravel(d, c);
+    rank_idx[pos + 1] = pidx;
+    mask[pidx] = 1;
+    pairof[pidx] = rank | (1 << 30);
+  }
+  const int sz = self ? 1 : 2;
+  if (pos + sz >= M) {
+    Mact[0] = pos + sz;
+    Mact[1] = rank + 1;
+  }
+}
+
 // Rank order of every representative of a plan (blockIdx.y): its sorted pairs
 // (main, nmain_b[plan] of them) merged with its nside self-conjugate
 // frequencies (unsorted, at most kSide).  Keys are a total order, so each element's place
-// is its index in its own list plus the count of smaller ones in the other.
-__global__ void k_merge_side(const SortEl* __restrict__ main, int64_t stride, const unsigned int* __restrict__ nmain_b,
-                             const SortEl* __restrict__ side, int nside, SortEl* __restrict__ out, int64_t nreps) {
+// is its index in its own list plus the count of smaller ones in the other;
+// pairs take two places of the selection and the others one, so its place
+// there follows from the same counts, without a scan.
+__global__ void k_merge_select(const SortEl* __restrict__ main, int64_t stride,
+                               const unsigned int* __restrict__ nmain_b, const SortEl* __restrict__ side, int nside,
+                               SortEl* __restrict__ out, int64_t nreps, Dims d, int64_t N,
+                               const PlanPtrs* __restrict__ pp, uint8_t* __restrict__ mask,
+                               int64_t* __restrict__ Mact, int* __restrict__ pairof) {
   const int b = blockIdx.y;
   const int64_t nmain = nmain_b[b];
   main += (int64_t)b * stride;
   side += (int64_t)b * kSide;
   out += (int64_t)b * nreps;
+  mask += (int64_t)b * N;
+  pairof += (int64_t)b * N;
+  Mact += 2 * b;
+  const int64_t M = pp[b].M;
+  int64_t* __restrict__ rank_idx = pp[b].rank;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < nmain) {
     const SortEl x = main[i];
     int c = 0;
     for (int t = 0; t < nside; ++t) c += el_less(side[t], x) ? 1 : 0;
     out[i + c] = x;
+    take_pair(d, x.idx, (int)(i + c), 2 * i + c, false, M, rank_idx, mask, pairof, Mact);
   } else if (i < nmain + nside) {
     const SortEl x = side[i - nmain];
     int r = 0;
@@ -382,6 +421,7 @@ __global__ void k_merge_side(const SortEl* __restrict__ main, int64_t stride, co
       }
     }
     out[r + lo] = x;
+    take_pair(d, x.idx, (int)(r + lo), 2 * lo + r, true, M, rank_idx, mask, pairof, Mact);
   }
 }
 
@@ -562,73 +602,32 @@ __global__ void k_bitonic_local(SortEl* el, int tile, int64_t seg, int64_t kglob
   for (int t = threadIdx.x; t < tile; t += blockDim.x) el[abase + t] = s[t];
 }
 
-// Pair-atomic selection in rank order (one workgroup per plan, blockIdx.x).
-// Also records, for every selected frequency, its pair index in rank order
-// (bit 30 set for the partner of the pair's representative); Mact[1] = number
-// of selected pairs.
-__global__ void k_select(const SortEl* __restrict__ el, int64_t stride, const unsigned int* __restrict__ nmain_b,
-                         int nside, Dims d, int64_t N, const PlanPtrs* __restrict__ pp, uint8_t* __restrict__ mask,
-                         int64_t* __restrict__ Mact, int* __restrict__ pairof) {
-  __shared__ int lds[32];
-  const int b = blockIdx.x;
-  const int64_t nreps = (int64_t)nmain_b[b] + nside;
-  el += (int64_t)b * stride;
-  mask += (int64_t)b * N;
-  pairof += (int64_t)b * N;
-  Mact += 2 * b;
-  const int64_t M = pp[b].M;
-  int64_t* __restrict__ rank = pp[b].rank;
-  int64_t base = 0;
-  for (int64_t c0 = 0; c0 < nreps; c0 += blockDim.x) {
-    int64_t i = c0 + threadIdx.x;
-    int sz = 0;
-    int64_t idx = 0, pidx = 0;
-    if (i < nreps) {
-      idx = el[i].idx;
-      int k[3], c[3];
-      unravel(d, idx, k);
-      conj_k(d, k, c);
-      pidx = ravel(d, c);
-      sz = pidx == idx ? 1 : 2;
-    }
-    int total;
-    int ex = block_excl_scan(sz, lds, &total);
-    int64_t pos = base + ex;
-    if (sz && pos < M) {
-      rank[pos] = idx;
-      mask[idx] = 1;
-      pairof[idx] = (int)i;
-      if (sz == 2) {
-        rank[pos + 1] = pidx;
-        mask[pidx] = 1;
-        pairof[pidx] = (int)i | (1 << 30);
-      }
-      if (pos + sz >= M) {
-        Mact[0] = pos + sz;
-        Mact[1] = i + 1;
-      }
-    }
-    base += total;
-    if (base >= M) break;
-  }
-}
-
 // Sorted pattern (increasing linear index) in three launches: per-chunk
 // counts, an exclusive scan of the counts, and the scatter of each chunk
 // (plan = blockIdx.y, for the scan blockIdx.x).
-constexpr int kCompactChunk = 4096;
+constexpr int kCompactChunk = 4096;  // 16 consecutive bytes per thread: one scan per chunk
+
+// The thread's 16 consecutive mask bytes as a bit mask (bytes past N: 0).
+__device__ __forceinline__ unsigned int mask16(const uint8_t* __restrict__ mask, int64_t i, int64_t N) {
+  unsigned int m = 0;
+  if (i + 16 <= N && ((uintptr_t)(mask + i) & 15) == 0) {
+    const uint4 v = *reinterpret_cast<const uint4*>(mask + i);
+    const unsigned int w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int q = 0; q < 16; ++q) m |= ((w[q / 4] >> (8 * (q % 4))) & 1u) << q;
+  } else {
+    for (int q = 0; q < 16; ++q)
+      if (i + q < N && mask[i + q]) m |= 1u << q;
+  }
+  return m;
+}
 
 __global__ __launch_bounds__(256) void k_compact_count(const uint8_t* __restrict__ mask, int64_t N,
                                                        int* __restrict__ ccount, int nchunk) {
   __shared__ int lds[32];
   mask += (int64_t)blockIdx.y * N;
   ccount += (int64_t)blockIdx.y * nchunk;
-  const int64_t c0 = (int64_t)blockIdx.x * kCompactChunk;
-  int n = 0;
-  for (int t = threadIdx.x; t < kCompactChunk; t += 256) {
-    const int64_t i = c0 + t;
-    n += (i < N) ? (int)mask[i] : 0;
-  }
+  const int n = __popc(mask16(mask, (int64_t)blockIdx.x * kCompactChunk + threadIdx.x * 16, N));
   int total;
   (void)block_excl_scan(n, lds, &total);
   if (threadIdx.x == 0) ccount[blockIdx.x] = total;
@@ -655,15 +654,13 @@ __global__ __launch_bounds__(256) void k_compact_scatter(const uint8_t* __restri
   mask += (int64_t)blockIdx.y * N;
   cbase += (int64_t)blockIdx.y * nchunk;
   int64_t* __restrict__ sorted = pp[blockIdx.y].sorted;
-  const int64_t c0 = (int64_t)blockIdx.x * kCompactChunk;
-  int base = cbase[blockIdx.x];
-  for (int t0 = 0; t0 < kCompactChunk; t0 += 256) {
-    const int64_t i = c0 + t0 + threadIdx.x;
-    const int f = (i < N) ? (int)mask[i] : 0;
-    int total;
-    const int ex = block_excl_scan(f, lds, &total);
-    if (f) sorted[base + ex] = i;
-    base += total;
+  const int64_t i = (int64_t)blockIdx.x * kCompactChunk + threadIdx.x * 16;
+  unsigned int m = mask16(mask, i, N);
+  int total;
+  int at = cbase[blockIdx.x] + block_excl_scan(__popc(m), lds, &total);
+  while (m) {
+    sorted[at++] = i + __ffs(m) - 1;
+    m &= m - 1;
   }
 }
 
@@ -1369,10 +1366,6 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
   }
   const int64_t nrank = seg + nselfc;  // per-plan stride of the rank order
   MOR_HIP_TRY(ranked.alloc(sc, (size_t)cnt * nrank));
-  k_merge_side<<<dim3((unsigned)((nrank + 255) / 256), nb), 256, 0, st>>>(keys, npow2, nsorted, side.p, (int)nselfc,
-                                                                          ranked.p, nrank);
-  MOR_LAUNCH_CHECK("merge_side");
-
   // 4. selection
   DevBuf<uint8_t> mask;
   DevBuf<int64_t> mact;
@@ -1382,8 +1375,9 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
   MOR_HIP_TRY(pairof.alloc(sc, (size_t)cnt * N));
   MOR_HIP_TRY(hipMemsetAsync(mask.p, 0, (size_t)cnt * N, st));
   MOR_HIP_TRY(hipMemsetAsync(pairof.p, 0, (size_t)cnt * N * sizeof(int), st));
-  k_select<<<nb, 1024, 0, st>>>(ranked.p, nrank, nsorted, (int)nselfc, d, N, pp.p, mask.p, mact.p, pairof.p);
-  MOR_LAUNCH_CHECK("select");
+  k_merge_select<<<dim3((unsigned)((nrank + 255) / 256), nb), 256, 0, st>>>(
+      keys, npow2, nsorted, side.p, (int)nselfc, ranked.p, nrank, d, N, pp.p, mask.p, mact.p, pairof.p);
+  MOR_LAUNCH_CHECK("merge_select");
   std::vector<int64_t> hm(2 * (size_t)cnt);
   std::vector<unsigned long long> hcount(cnt);
   MOR_HIP_TRY(hipMemcpyAsync(hm.data(), mact.p, 2 * cnt * sizeof(int64_t), hipMemcpyDeviceToHost, st));
