@@ -24,7 +24,9 @@
  *    stream).  Calls that return host results synchronise that stream.
  *  - The solve calls keep a workspace per (device, stream): device buffers
  *    and a pinned host staging buffer (at most 64 MiB) for their small
- *    transfers, grown on demand and held until the process ends
+ *    transfers, grown on demand, and up to three further streams on which
+ *    a call's independent grids or runs iterate (joined to the call's stream
+ *    before it returns), all held until the process ends
  *    (mor_solve_noalloc uses none of it).
  */
 #ifndef MOR_H
@@ -184,9 +186,9 @@ typedef struct {
  * FP64 sums in every mode):
  *   MOR_PREC_FP32    FP32 transforms and fields (default; specialised kernels)
  *   MOR_PREC_BF16X3  split-bf16 partial DFT on MFMA, FP32 accumulate
- *   MOR_PREC_FP64    FP64 transforms, Green operator and Hooke law (generic
- *                    kernels; Hooke phases, FFT transform and grid schedule
- *                    only, else MOR_E_UNSUPPORTED).  For tolerances below what
+ *   MOR_PREC_FP64    FP64 transforms, Green operator and Hooke law (Hooke
+ *                    phases, FFT transform and grid schedule only, else
+ *                    MOR_E_UNSUPPORTED).  For tolerances below what
  *                    FP32 reaches (the paper's examples stop at 1e-8); field
  *                    and coefficient outputs are rounded to FP32. */
 enum { MOR_PREC_FP32 = 0, MOR_PREC_BF16X3 = 1, MOR_PREC_FP64 = 2 };
@@ -203,7 +205,7 @@ typedef struct {
   int32_t precision;    /* MOR_PREC_*                                            */
   int32_t transform;    /* MOR_TRANSFORM_*                                       */
   int32_t check_every;  /* iterations between device->host convergence polls;
-                           0 -> library default                                  */
+                           0 -> polls placed by the progress of the residuals    */
   const float* warm_start; /* device complex64 [B][ncomp][n_coeff] strain
                               coefficients in plan coefficient order (the
                               zero frequency entry is ignored and set to
@@ -256,7 +258,9 @@ mor_status mor_solve(mor_plan_t plan, const double* macro_strain, int64_t B,
  * buffer of the solve (coefficients, transform lines, residual and stress
  * partials, per-RVE states, the J2 state of Hooke/J2 solves) is carved from
  * one library-owned device array of MOR_NOALLOC_SCRATCH_BYTES per GPU,
- * which the GPU holds from the library's load until the process ends.
+ * which the GPU holds from the library's load until the process ends, with
+ * a smaller array beside it for the residual partials that the row kernels
+ * read (it does not count against the limit).
  *   - A solve that needs more than the array returns MOR_E_INVALID_ARG
  *     before any kernel runs (call again with fewer RVEs).
  *   - opts->use_graph must be 0 (MOR_E_UNSUPPORTED otherwise); per-kernel
@@ -452,8 +456,10 @@ mor_status mor_warm_apply(const mor_plan_t* plans, int64_t nplans, const int64_t
  * except the row kernel with J2 phases on 512-point last axes (variant 4)
  * and 384-point last axes (variant 2), whose radix-4 register passes leave
  * room for the plastic state; mor_tune_get reports a selection, or 0 when
- * there is none.  The selection is per process, shared by all threads
- * and devices.
+ * there is none.  At its default variant a row length with few
+ * workgroups in the call runs a kernel with one component per wavefront
+ * instead, equal to the variants up to FP32 rounding.  The selection is per process, shared by
+ * all threads and devices.
  *   kernel  MOR_KERNEL_ROW (last axis) or MOR_KERNEL_COL (axis 0)
  *   ndim    2 or 3; length = the grid's last-axis length n[ndim-1] (row) or
  *           its axis-0 length n[0] (column)
