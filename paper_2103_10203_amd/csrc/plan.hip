@@ -119,8 +119,8 @@ struct PlanPtrs {
   cpx<float>* tw;
   cpx<double>* tw64;
   PlanDev* dev;
-  int64_t M, nslots;
-  int32_t ncol, nlast;
+  int64_t M;
+  PlanDev desc;  // the plan's descriptor; k_tab_scan fills in the table sizes
 };
 
 // Offsets of the integer tables inside PlanPtrs::ints (the same for every
@@ -129,29 +129,15 @@ struct IntLayout {
   int32_t col_k, col_last, col_off, last_k, last_off, coef_k0;
 };
 
-template <typename T>
-__device__ __forceinline__ cpx<T>* plan_tw(const PlanPtrs& q);
-template <>
-__device__ __forceinline__ cpx<float>* plan_tw<float>(const PlanPtrs& q) { return q.tw; }
-template <>
-__device__ __forceinline__ cpx<double>* plan_tw<double>(const PlanPtrs& q) { return q.tw64; }
-
 // ------------------------------------------------------------------ kernels
 
-__global__ void k_twiddle_f64(cpx<double>* tw, int n) {
-  int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  double s, c;
-  sincospi(2.0 * (double)t / (double)n, &s, &c);
-  tw[t] = {c, -s};
-}
-
-// The four solver twiddle tables in one launch, packed tw0 [n0] | tw1 [n1] |
-// twh [nh] | rtw [nl], each exp(-2 pi i t / length) evaluated in FP64 (and
-// rounded for the FP32 tables).
-template <typename T>
+// The four twiddle tables of a plan, packed tw0 [n0] | tw1 [n1] | twh [nh] |
+// rtw [nl], each exp(-2 pi i t / length) evaluated in FP64, and rounded for the
+// FP32 tables (FP64 and FP32 in one launch; plan = blockIdx.y).  The spectrum of
+// the phase maps takes its twiddles from the first plan's.
 __global__ void k_twiddle4(const PlanPtrs* __restrict__ pp, int n0, int n1, int nh, int nl) {
-  cpx<T>* __restrict__ tw = plan_tw<T>(pp[blockIdx.y]);
+  cpx<float>* __restrict__ tw = pp[blockIdx.y].tw;
+  cpx<double>* __restrict__ tw64 = pp[blockIdx.y].tw64;
   int t = blockIdx.x * blockDim.x + threadIdx.x;
   int n;
   int u = t;
@@ -168,7 +154,8 @@ __global__ void k_twiddle4(const PlanPtrs* __restrict__ pp, int n0, int n1, int 
   }
   double s, c;
   sincospi(2.0 * (double)u / (double)n, &s, &c);
-  tw[t] = {(T)c, (T)(-s)};
+  tw64[t] = {c, -s};
+  tw[t] = {(float)c, (float)(-s)};
 }
 
 // Phase maps [batch][N] -> each plan's copy of g and the complex FP64 input
@@ -667,10 +654,11 @@ __global__ __launch_bounds__(256) void k_compact_scatter(const uint8_t* __restri
 // Slot tables of the warm-start network: slot s = pair s+1 in rank order
 // (pair 0 is xi = 0): representative's linear index and g^(rep) / count.
 __global__ void k_slots(const SortEl* __restrict__ el, int64_t stride, const cpx<double>* __restrict__ S, int64_t N,
-                        const unsigned long long* count, const PlanPtrs* __restrict__ pp) {
+                        const unsigned long long* count, const PlanPtrs* __restrict__ pp,
+                        const int64_t* __restrict__ Mact) {
   const int b = blockIdx.y;
   int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= pp[b].nslots) return;
+  if (s >= Mact[2 * b + 1] - 1) return;  // all selected pairs but xi = 0
   el += (int64_t)b * stride;
   S += (int64_t)b * N;
   count += b;
@@ -708,6 +696,8 @@ __global__ __launch_bounds__(256) void k_tab_count(const uint8_t* __restrict__ m
     if (n) atomicAdd(&lastcnt[kh], n);
   }
 }
+
+static_assert(sizeof(PlanDev) % 4 == 0, "PlanDev is copied in 4-byte words");
 
 // One workgroup per plan (blockIdx.x): column and last-axis indices and offsets.
 __global__ void k_tab_scan(const int* __restrict__ cnt, const int* __restrict__ lastcnt, Dims d, int ncolall, int nkh,
@@ -758,12 +748,22 @@ __global__ void k_tab_scan(const int* __restrict__ cnt, const int* __restrict__ 
     lb += tl;
   }
   if (threadIdx.x == 0) meta[1] = lb;  // nlast
+  // the plan's descriptor with its table sizes
+  const uint32_t* __restrict__ from = reinterpret_cast<const uint32_t*>(&pp[b].desc);
+  uint32_t* __restrict__ to = reinterpret_cast<uint32_t*>(pp[b].dev);
+  for (int w = threadIdx.x; w < (int)(sizeof(PlanDev) / 4); w += blockDim.x) {
+    const int at = 4 * w;
+    to[w] = at == (int)offsetof(PlanDev, ncol)    ? (uint32_t)jb
+            : at == (int)offsetof(PlanDev, nlast) ? (uint32_t)lb
+            : at == (int)offsetof(PlanDev, ncoef) ? (uint32_t)ob
+                                                  : from[w];
+  }
 }
 
 __global__ void k_tab_groups(const int* __restrict__ col_kh, const int* __restrict__ lastidx, int ncolall, int nkh,
-                             const PlanPtrs* __restrict__ pp, IntLayout il) {
+                             const int* __restrict__ meta, const PlanPtrs* __restrict__ pp, IntLayout il) {
   const int b = blockIdx.y;
-  const int ncol = pp[b].ncol, nlast = pp[b].nlast;
+  const int ncol = meta[4 * b], nlast = meta[4 * b + 1];
   int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j > ncol) return;
   col_kh += (int64_t)b * ncolall;
@@ -897,15 +897,6 @@ __global__ __launch_bounds__(256) void k_tab_fill(const uint8_t* __restrict__ ma
     }
     e += __popcll(bal);
   }
-}
-
-// Each plan's PlanDev from an array staged in device memory (blockIdx.x = plan).
-static_assert(sizeof(PlanDev) % 4 == 0, "PlanDev is copied in 4-byte words");
-__global__ void k_put_plandev(const PlanDev* __restrict__ src, const PlanPtrs* __restrict__ pp) {
-  const int b = blockIdx.x;
-  const uint32_t* __restrict__ from = reinterpret_cast<const uint32_t*>(src + b);
-  uint32_t* __restrict__ to = reinterpret_cast<uint32_t*>(pp[b].dev);
-  for (int w = threadIdx.x; w < (int)(sizeof(PlanDev) / 4); w += blockDim.x) to[w] = from[w];
 }
 
 bool size_ok(int64_t n) {
@@ -1109,8 +1100,8 @@ static void host_parallel(int64_t n, size_t bytes, F fn) {
 // maps[0..cnt) (each N bytes, already checked), staged through `pinned`
 // (cnt N bytes of pinned host memory, or NULL to copy the maps one by one).
 // Every step is one launch over the whole batch (plan = a grid dimension of
-// the launch), with two host synchronisations for the sizes of the per-plan
-// tables.  Scratch: about 30 N + 16 N' bytes per plan (N' the power of two at
+// the launch), with one host synchronisation on the way, for the length of the
+// sort, and one at the end, which reads the table sizes back.  Scratch: about 30 N + 16 N' bytes per plan (N' the power of two at
 // or above the number of conjugate pairs).
 static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint8_t* const* maps, uint8_t* pinned,
                                    hipStream_t st) {
@@ -1251,18 +1242,76 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
     h.tw64 = Q->d_tw64;
     h.dev = Q->d_dev;
     h.M = Q->M;
+
+    PlanDev& v = Q->dev;
+    v = PlanDev{};
+    v.ndim = nd;
+    v.n0 = n0;
+    v.n1 = n1;
+    v.n2 = nd == 3 ? P0.n[2] : 1;
+    v.N = (int32_t)N;
+    v.nlen = nlen;
+    v.rows = (int32_t)(N / nlen);
+    v.inv_N = (float)(1.0 / (double)N);
+    v.g = Q->d_g;
+    v.col_k = Q->d_ints + il.col_k;
+    v.col_last = Q->d_ints + il.col_last;
+    v.col_off = Q->d_ints + il.col_off;
+    v.last_k = Q->d_ints + il.last_k;
+    v.last_off = Q->d_ints + il.last_off;
+    v.coef_k0 = Q->d_ints + il.coef_k0;
+    v.coef_n = Q->d_coef_n;
+    v.coef_flag = Q->d_coef_flag;
+    v.tw0 = Q->d_tw;
+    v.tw1 = v.tw0 + n0;
+    v.twh = v.tw1 + n1;
+    v.rtw = v.twh + nlen / 2;
+    v.coef_n64 = Q->d_coef_n64;
+    v.tw0_64 = Q->d_tw64;
+    v.tw1_64 = v.tw0_64 + n0;
+    v.twh_64 = v.tw1_64 + n1;
+    v.rtw_64 = v.twh_64 + nlen / 2;
+    fft_make_desc(n0, &v.fd0);
+    fft_make_desc(n1, &v.fd1);
+    fft_make_desc(nlen / 2, &v.fdh);
+    h.desc = v;
   }
   MOR_HIP_TRY(hipMemcpyAsync(pp.p, hp.data(), cnt * sizeof(PlanPtrs), hipMemcpyHostToDevice, st));
 
+  // Everything that starts as zero lies in one block, cleared by one launch; the
+  // sizes that the host reads back at the end come first.  One plan is a chain
+  // of small launches: with seven clears, twiddles per axis and precision, two
+  // more uploads and a synchronisation for each set of sizes a 512^2 plan took 454
+  // us, now 347 us, and 256 plans of 256^2 with their features 3.22, now 3.02 ms.
+  const size_t nhist = (size_t)cnt * (kHist1 + kHist2);
+  size_t zat = 0;
+  auto ztake = [&zat](size_t bytes) {
+    const size_t o = zat;
+    zat += (bytes + 255) / 256 * 256;
+    return o;
+  };
+  const size_t z_sizes = ztake((size_t)cnt * 40), z_cc = ztake((size_t)cnt * 4), z_side = ztake((size_t)cnt * 4),
+               z_hist = ztake(nhist * 4), z_last = ztake((size_t)cnt * nkh * 4), z_mask = ztake((size_t)cnt * N),
+               z_pair = ztake((size_t)cnt * N * 4);
+  DevBuf<unsigned char> zeroed;
+  MOR_HIP_TRY(zeroed.alloc(sc, zat));
+  MOR_HIP_TRY(hipMemsetAsync(zeroed.p, 0, zat, st));
+  int64_t* mact = (int64_t*)(zeroed.p + z_sizes);                      // [cnt][2] selected: frequencies, pairs
+  unsigned long long* count = (unsigned long long*)(mact + 2 * cnt);   // [cnt] inclusion points
+  int* meta = (int*)(count + cnt);                                     // [cnt][4] ncol, nlast, ncoef, -
+  unsigned int* ccount = (unsigned int*)(zeroed.p + z_cc);             // [cnt] sorted pairs
+  unsigned int* nside = (unsigned int*)(zeroed.p + z_side);            // [cnt] self-conjugate frequencies
+  unsigned int *hist1 = (unsigned int*)(zeroed.p + z_hist), *hist2 = hist1 + (size_t)cnt * kHist1;
+  int* lastcnt = (int*)(zeroed.p + z_last);
+  uint8_t* mask = zeroed.p + z_mask;
+  int* pairof = (int*)(zeroed.p + z_pair);
+
   // 1. FP64 spectrum of every phase map ([cnt][N], each axis batched as lines)
+  k_twiddle4<<<dim3((ntw + 255) / 256, nb), 256, 0, st>>>(pp.p, n0, n1, nlen / 2, nlen);
+  MOR_LAUNCH_CHECK("twiddle");
   DevBuf<cpx<double>> S;
-  DevBuf<cpx<double>> tw64;
-  DevBuf<unsigned long long> count;
   MOR_HIP_TRY(S.alloc(sc, (size_t)cnt * N));
-  MOR_HIP_TRY(tw64.alloc(sc, 1024));
-  MOR_HIP_TRY(count.alloc(sc, cnt));
-  MOR_HIP_TRY(hipMemsetAsync(count.p, 0, cnt * sizeof(unsigned long long), st));
-  k_g_to_cplx<<<dim3((unsigned)((N + 255) / 256), nb), 256, 0, st>>>(G.p, pp.p, S.p, N, count.p);
+  k_g_to_cplx<<<dim3((unsigned)((N + 255) / 256), nb), 256, 0, st>>>(G.p, pp.p, S.p, N, count);
   MOR_LAUNCH_CHECK("g_to_cplx");
   for (int a = 0; a < nd; ++a) {
     int na = P0.n[a];
@@ -1271,12 +1320,11 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
     for (int b = a + 1; b < nd; ++b) inner *= P0.n[b];
     FftDesc fd;
     fft_make_desc(na, &fd);
-    k_twiddle_f64<<<(na + 255) / 256, 256, 0, st>>>(tw64.p, na);
-    MOR_LAUNCH_CHECK("twiddle_f64");
+    const cpx<double>* tw = a == 0 ? P[0]->dev.tw0_64 : a == 1 ? P[0]->dev.tw1_64 : P[0]->dev.rtw_64;
     int lpw = std::max(1, 1024 / na);
     int64_t nlines = (int64_t)outer * inner;
     size_t sh = (size_t)(na + 2 * lpw * na) * sizeof(cpx<double>);
-    k_fft_axis_f64<<<(unsigned)((nlines + lpw - 1) / lpw), 256, sh, st>>>(S.p, outer, na, inner, lpw, fd, tw64.p);
+    k_fft_axis_f64<<<(unsigned)((nlines + lpw - 1) / lpw), 256, sh, st>>>(S.p, outer, na, inner, lpw, fd, tw);
     MOR_LAUNCH_CHECK("fft_axis_f64");
   }
 
@@ -1290,13 +1338,8 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
   while (npow2 < nmain) npow2 <<= 1;
   const int64_t nel = (int64_t)cnt * npow2;
   DevBuf<SortEl> el, side, ranked, cand;
-  DevBuf<unsigned int> nout, ccount;
-  DevBuf<unsigned int> hist;
   MOR_HIP_TRY(el.alloc(sc, nel));
   MOR_HIP_TRY(side.alloc(sc, (size_t)cnt * kSide));
-  MOR_HIP_TRY(nout.alloc(sc, 2 * (size_t)cnt));
-  MOR_HIP_TRY(ccount.alloc(sc, (size_t)cnt));
-  MOR_HIP_TRY(hipMemsetAsync(nout.p, 0, 2 * cnt * sizeof(unsigned int), st));
   {
     const int nkb = (int)((N + 255) / 256);
     DevBuf<int> boff;
@@ -1305,8 +1348,8 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
     MOR_LAUNCH_CHECK("rep_counts");
     k_compact_scan<<<1, 1024, 0, st>>>(boff.p, nkb);  // exclusive scan: block offsets
     MOR_LAUNCH_CHECK("rep_scan");
-    k_keys<<<dim3((unsigned)nkb, nb), 256, 0, st>>>(S.p, d, N, count.p, radial.p, el.p, npow2, boff.p, side.p,
-                                                    nout.p + cnt);
+    k_keys<<<dim3((unsigned)nkb, nb), 256, 0, st>>>(S.p, d, N, count, radial.p, el.p, npow2, boff.p, side.p,
+                                                    nside);
     MOR_LAUNCH_CHECK("keys");
   }
 
@@ -1316,21 +1359,16 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
   // fewer than all pairs (large M, or many equal keys at the cut) every pair
   // is sorted instead.  Either way the rank order of the selected pairs is
   // the total order of all pairs.
-  const size_t nhist = (size_t)cnt * (kHist1 + kHist2);
-  MOR_HIP_TRY(hist.alloc(sc, nhist));
-  unsigned int *hist1 = hist.p, *hist2 = hist.p + (size_t)cnt * kHist1;
-  MOR_HIP_TRY(hipMemsetAsync(hist.p, 0, nhist * sizeof(unsigned int), st));
   const dim3 gtop((unsigned)((nmain + kTopkChunk - 1) / kTopkChunk), nb);
   k_topk_hist<1><<<gtop, 256, 0, st>>>(el.p, npow2, nmain, pp.p, hist1, hist2);
   MOR_LAUNCH_CHECK("topk_hist");
   k_topk_hist<2><<<gtop, 256, 0, st>>>(el.p, npow2, nmain, pp.p, hist1, hist2);
   MOR_LAUNCH_CHECK("topk_hist");
   MOR_HIP_TRY(cand.alloc(sc, nel));
-  MOR_HIP_TRY(hipMemsetAsync(ccount.p, 0, cnt * sizeof(unsigned int), st));
-  k_topk_compact<<<gtop, 256, 0, st>>>(el.p, npow2, nmain, pp.p, hist1, hist2, cand.p, npow2, ccount.p);
+  k_topk_compact<<<gtop, 256, 0, st>>>(el.p, npow2, nmain, pp.p, hist1, hist2, cand.p, npow2, ccount);
   MOR_LAUNCH_CHECK("topk_compact");
   std::vector<unsigned int> hcc((size_t)cnt);
-  MOR_HIP_TRY(hipMemcpyAsync(hcc.data(), ccount.p, cnt * sizeof(unsigned int), hipMemcpyDeviceToHost, st));
+  MOR_HIP_TRY(hipMemcpyAsync(hcc.data(), ccount, cnt * sizeof(unsigned int), hipMemcpyDeviceToHost, st));
   MOR_HIP_TRY(hipStreamSynchronize(st));
   int64_t maxc = 0;
   for (int b = 0; b < cnt; ++b) maxc = std::max<int64_t>(maxc, hcc[b]);
@@ -1338,11 +1376,11 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
   while (cpow2 < maxc) cpow2 <<= 1;
   SortEl* keys = cand.p;  // the sorted segments, stride npow2
   int64_t seg = cpow2;
-  unsigned int* nsorted = ccount.p;
+  unsigned int* nsorted = ccount;
   if (2 * cpow2 > npow2) {  // not worth it: sort every pair
     keys = el.p;
     seg = npow2;
-    k_fill_u32<<<(cnt + 255) / 256, 256, 0, st>>>(ccount.p, cnt, (unsigned int)nmain);
+    k_fill_u32<<<(cnt + 255) / 256, 256, 0, st>>>(ccount, cnt, (unsigned int)nmain);
     MOR_LAUNCH_CHECK("fill_counts");
   }
   k_fill_sentinel<<<dim3((unsigned)((seg + 255) / 256), nb), 256, 0, st>>>(keys, nsorted, seg, npow2);
@@ -1366,141 +1404,67 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
   }
   const int64_t nrank = seg + nselfc;  // per-plan stride of the rank order
   MOR_HIP_TRY(ranked.alloc(sc, (size_t)cnt * nrank));
-  // 4. selection
-  DevBuf<uint8_t> mask;
-  DevBuf<int64_t> mact;
-  DevBuf<int> pairof;
-  MOR_HIP_TRY(mask.alloc(sc, (size_t)cnt * N));
-  MOR_HIP_TRY(mact.alloc(sc, 2 * (size_t)cnt));
-  MOR_HIP_TRY(pairof.alloc(sc, (size_t)cnt * N));
-  MOR_HIP_TRY(hipMemsetAsync(mask.p, 0, (size_t)cnt * N, st));
-  MOR_HIP_TRY(hipMemsetAsync(pairof.p, 0, (size_t)cnt * N * sizeof(int), st));
+  // 4. selection, and the slot tables of the warm-start network (no plan has
+  // more slots than M; the device knows how many)
   k_merge_select<<<dim3((unsigned)((nrank + 255) / 256), nb), 256, 0, st>>>(
-      keys, npow2, nsorted, side.p, (int)nselfc, ranked.p, nrank, d, N, pp.p, mask.p, mact.p, pairof.p);
+      keys, npow2, nsorted, side.p, (int)nselfc, ranked.p, nrank, d, N, pp.p, mask, mact, pairof);
   MOR_LAUNCH_CHECK("merge_select");
-  std::vector<int64_t> hm(2 * (size_t)cnt);
-  std::vector<unsigned long long> hcount(cnt);
-  MOR_HIP_TRY(hipMemcpyAsync(hm.data(), mact.p, 2 * cnt * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  MOR_HIP_TRY(hipMemcpyAsync(hcount.data(), count.p, cnt * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-  MOR_HIP_TRY(hipStreamSynchronize(st));
-
-  // sizes of the selection
-  int64_t max_slots = 0;
-  for (int b = 0; b < cnt; ++b) {
-    mor_plan* Q = P[b];
-    Q->M_actual = hm[2 * b];
-    Q->nslots = hm[2 * b + 1] - 1;
-    Q->count = (int64_t)hcount[b];
-    if (Q->M_actual < 1 || Q->M_actual > Q->M + 1 || Q->nslots < 0 || Q->nslots >= Q->M_actual) {
-      mor_set_error("mor_plan: selection sizes outside their bounds");
-      return MOR_E_DEVICE;
-    }
-    max_slots = std::max(max_slots, Q->nslots);
-    hp[b].nslots = Q->nslots;
-  }
-  MOR_HIP_TRY(hipMemcpyAsync(pp.p, hp.data(), cnt * sizeof(PlanPtrs), hipMemcpyHostToDevice, st));
-
-  // slot tables of the warm-start network
-  if (max_slots > 0) {
-    k_slots<<<dim3((unsigned)((max_slots + 255) / 256), nb), 256, 0, st>>>(ranked.p, nrank, S.p, N, count.p, pp.p);
-    MOR_LAUNCH_CHECK("slots");
-  }
+  int64_t mmax = 1;
+  for (int b = 0; b < cnt; ++b) mmax = std::max(mmax, P[b]->M);
+  k_slots<<<dim3((unsigned)((mmax + 255) / 256), nb), 256, 0, st>>>(ranked.p, nrank, S.p, N, count, pp.p, mact);
+  MOR_LAUNCH_CHECK("slots");
 
   // 5. sorted pattern
   {
     const int nchunk = (int)((N + kCompactChunk - 1) / kCompactChunk);
     DevBuf<int> ccount;
     MOR_HIP_TRY(ccount.alloc(sc, (size_t)cnt * nchunk));
-    k_compact_count<<<dim3(nchunk, nb), 256, 0, st>>>(mask.p, N, ccount.p, nchunk);
+    k_compact_count<<<dim3(nchunk, nb), 256, 0, st>>>(mask, N, ccount.p, nchunk);
     k_compact_scan<<<nb, 1024, 0, st>>>(ccount.p, nchunk);
-    k_compact_scatter<<<dim3(nchunk, nb), 256, 0, st>>>(mask.p, N, ccount.p, nchunk, pp.p);
+    k_compact_scatter<<<dim3(nchunk, nb), 256, 0, st>>>(mask, N, ccount.p, nchunk, pp.p);
     MOR_LAUNCH_CHECK("compact");
   }
 
   // 6. tables
-  DevBuf<int> cntc, lastcnt, colidx, col_kh, lastidx, meta;
+  DevBuf<int> cntc, colidx, col_kh, lastidx;
   MOR_HIP_TRY(cntc.alloc(sc, (size_t)cnt * ncolall));
-  MOR_HIP_TRY(lastcnt.alloc(sc, (size_t)cnt * nkh));
   MOR_HIP_TRY(colidx.alloc(sc, (size_t)cnt * ncolall));
   MOR_HIP_TRY(col_kh.alloc(sc, (size_t)cnt * ncolall));
   MOR_HIP_TRY(lastidx.alloc(sc, (size_t)cnt * nkh));
-  MOR_HIP_TRY(meta.alloc(sc, 4 * (size_t)cnt));
-  MOR_HIP_TRY(hipMemsetAsync(lastcnt.p, 0, (size_t)cnt * nkh * sizeof(int), st));
-  k_tab_count<<<dim3((ncolall + 3) / 4, nb), 256, 0, st>>>(mask.p, d, N, ncolall, nkh, cntc.p, lastcnt.p);
+  k_tab_count<<<dim3((ncolall + 3) / 4, nb), 256, 0, st>>>(mask, d, N, ncolall, nkh, cntc.p, lastcnt);
   MOR_LAUNCH_CHECK("tab_count");
-  k_tab_scan<<<nb, 1024, 0, st>>>(cntc.p, lastcnt.p, d, ncolall, nkh, colidx.p, col_kh.p, lastidx.p, meta.p, pp.p, il);
+  k_tab_scan<<<nb, 1024, 0, st>>>(cntc.p, lastcnt, d, ncolall, nkh, colidx.p, col_kh.p, lastidx.p, meta, pp.p, il);
   MOR_LAUNCH_CHECK("tab_scan");
-  std::vector<int> hmeta(4 * (size_t)cnt);
-  MOR_HIP_TRY(hipMemcpyAsync(hmeta.data(), meta.p, 4 * cnt * sizeof(int), hipMemcpyDeviceToHost, st));
-  MOR_HIP_TRY(hipStreamSynchronize(st));
+  k_tab_groups<<<dim3((ncolall + 1 + 255) / 256, nb), 256, 0, st>>>(col_kh.p, lastidx.p, ncolall, nkh, meta, pp.p, il);
+  MOR_LAUNCH_CHECK("tab_groups");
+  k_tab_fill<<<dim3((ncolall + 3) / 4, nb), 256, 0, st>>>(mask, d, N, ncolall, colidx.p, pairof, P0.gamma_kind, pp.p,
+                                                          il);
+  MOR_LAUNCH_CHECK("tab_fill");
 
-  int max_col = 0;
-  std::vector<PlanDev> hdev(cnt);
+  // sizes of the selection and of the tables
+  std::vector<int64_t> back(5 * (size_t)cnt);
+  MOR_HIP_TRY(hipMemcpyAsync(back.data(), mact, (size_t)cnt * 40, hipMemcpyDeviceToHost, st));
+  MOR_HIP_TRY(hipStreamSynchronize(st));
+  const int64_t* hcount = back.data() + 2 * (size_t)cnt;
+  const int* hmeta = (const int*)(back.data() + 3 * (size_t)cnt);
   for (int b = 0; b < cnt; ++b) {
     mor_plan* Q = P[b];
+    Q->M_actual = back[2 * b];
+    Q->nslots = back[2 * b + 1] - 1;
+    Q->count = hcount[b];
+    if (Q->M_actual < 1 || Q->M_actual > Q->M + 1 || Q->nslots < 0 || Q->nslots >= Q->M_actual) {
+      mor_set_error("mor_plan: selection sizes outside their bounds");
+      return MOR_E_DEVICE;
+    }
     const int ncol = hmeta[4 * b], nlast = hmeta[4 * b + 1], ncoef = hmeta[4 * b + 2];
-    max_col = std::max(max_col, ncol);
     if (ncol < 0 || ncol > ncolall || nlast < 0 || nlast > nkh || ncoef < 0 || ncoef > Q->M_actual) {
       mor_set_error("mor_plan: table sizes outside their bounds");
       return MOR_E_DEVICE;
     }
-    hp[b].ncol = ncol;
-    hp[b].nlast = nlast;
-
-    PlanDev& v = Q->dev;
-    v = PlanDev{};
-    v.ndim = nd;
-    v.n0 = n0;
-    v.n1 = n1;
-    v.n2 = nd == 3 ? P0.n[2] : 1;
-    v.N = (int32_t)N;
-    v.nlen = nlen;
-    v.rows = (int32_t)(N / nlen);
-    v.ncol = ncol;
-    v.nlast = nlast;
-    v.ncoef = ncoef;
-    v.inv_N = (float)(1.0 / (double)N);
-    v.g = Q->d_g;
-    v.col_k = Q->d_ints + il.col_k;
-    v.col_last = Q->d_ints + il.col_last;
-    v.col_off = Q->d_ints + il.col_off;
-    v.last_k = Q->d_ints + il.last_k;
-    v.last_off = Q->d_ints + il.last_off;
-    v.coef_k0 = Q->d_ints + il.coef_k0;
-    v.coef_n = Q->d_coef_n;
-    v.coef_flag = Q->d_coef_flag;
-    v.tw0 = Q->d_tw;
-    v.tw1 = v.tw0 + n0;
-    v.twh = v.tw1 + n1;
-    v.rtw = v.twh + nlen / 2;
-    v.coef_n64 = Q->d_coef_n64;
-    v.tw0_64 = Q->d_tw64;
-    v.tw1_64 = v.tw0_64 + n0;
-    v.twh_64 = v.tw1_64 + n1;
-    v.rtw_64 = v.twh_64 + nlen / 2;
-    fft_make_desc(n0, &v.fd0);
-    fft_make_desc(n1, &v.fd1);
-    fft_make_desc(nlen / 2, &v.fdh);
-    hdev[b] = v;
+    Q->dev.ncol = ncol;
+    Q->dev.nlast = nlast;
+    Q->dev.ncoef = ncoef;
   }
-  MOR_HIP_TRY(hipMemcpyAsync(pp.p, hp.data(), cnt * sizeof(PlanPtrs), hipMemcpyHostToDevice, st));
-  k_tab_groups<<<dim3((max_col + 1 + 255) / 256, nb), 256, 0, st>>>(col_kh.p, lastidx.p, ncolall, nkh, pp.p, il);
-  MOR_LAUNCH_CHECK("tab_groups");
-  k_tab_fill<<<dim3((ncolall + 3) / 4, nb), 256, 0, st>>>(mask.p, d, N, ncolall, colidx.p, pairof.p, P0.gamma_kind,
-                                                          pp.p, il);
-  MOR_LAUNCH_CHECK("tab_fill");
-
-  // twiddles of the solver transforms, and each plan's device descriptor
-  k_twiddle4<float><<<dim3((ntw + 255) / 256, nb), 256, 0, st>>>(pp.p, n0, n1, nlen / 2, nlen);
-  MOR_LAUNCH_CHECK("twiddle_f32");
-  k_twiddle4<double><<<dim3((ntw + 255) / 256, nb), 256, 0, st>>>(pp.p, n0, n1, nlen / 2, nlen);
-  MOR_LAUNCH_CHECK("twiddle_f64");
-  DevBuf<PlanDev> dstage;
-  MOR_HIP_TRY(dstage.alloc(sc, cnt));
-  MOR_HIP_TRY(hipMemcpyAsync(dstage.p, hdev.data(), cnt * sizeof(PlanDev), hipMemcpyHostToDevice, st));
-  k_put_plandev<<<nb, 64, 0, st>>>(dstage.p, pp.p);
-  MOR_LAUNCH_CHECK("put_plandev");
-  MOR_HIP_TRY(hipStreamSynchronize(st));
   return MOR_OK;
 }
 
@@ -1516,7 +1480,7 @@ static size_t plan_scratch_bytes(const mor_grid* grid, int64_t N) {
   // keys and candidates (16 npow2 each), the rank order (at most npow2 +
   // 2^ndim entries), spectrum, masks and tables
   return (size_t)(22 * N + 48 * npow2 + 16 * nselfc + 16 * kSide + 12 * ncolall + 8 * (nlen / 2 + 1) +
-                  4 * (N / 4096 + 1) + 4 * (kHist1 + kHist2) + 16 + sizeof(PlanPtrs) + sizeof(PlanDev) + 64);
+                  4 * (N / 4096 + 1) + 4 * (kHist1 + kHist2) + 16 + sizeof(PlanPtrs) + 64);
 }
 
 // Shared by mor_plan_create (count 1) and mor_plan_create_batch.
