@@ -222,6 +222,12 @@ __global__ void k_fft_axis_f64(cpx<double>* __restrict__ S, int outer, int na, i
 // blockIdx.y = plan: its spectrum at S + b N, its elements at out + b stride.
 constexpr int kSide = 8;
 
+// Most comparisons of the order by counting (all plans of a launch), above one
+// bitonic tile.  Construction with the network / by counting: one 512^2 plan
+// with 6.6 k pairs 312 / 282 us, with 11 k 330 / 289, one 256^2 with 2.1 k 293 /
+// 270; at 1.3e8 comparisons, 16 plans of 2.9 k pairs 401 / 402, 28 of 2.1 k 472 / 476.
+constexpr double kRankPairs = 134217728.0;
+
 // Fixed radial pattern (Sec. 4.1): L lines through xi = 0 at angles l pi / L
 // from the axis-1 direction.  One thread per (line = blockIdx.y, step u along
 // the line's major axis); the point on the minor axis is the nearest integer
@@ -587,6 +593,38 @@ __global__ void k_bitonic_local(SortEl* el, int tile, int64_t seg, int64_t kglob
     for (int j = tile >> 1; j > 0; j >>= 1) step(kglob, j);
   }
   for (int t = threadIdx.x; t < tile; t += blockDim.x) el[abase + t] = s[t];
+}
+
+// Order by counting: an element's place is the number of smaller ones (the
+// keys are a total order).  k_rank_count adds up one 256 x 256 block of the
+// comparisons (plan = blockIdx.z), k_rank_place moves the elements.  n^2 work, but all
+// of it independent, in two launches, where the bitonic network beyond one tile is
+// a chain of up to dozens on a few workgroups.
+__global__ __launch_bounds__(256) void k_rank_count(const SortEl* __restrict__ el, int64_t stride,
+                                                    const unsigned int* __restrict__ n_b,
+                                                    unsigned int* __restrict__ place, int64_t pstride) {
+  __shared__ SortEl s[256];
+  const int n = (int)n_b[blockIdx.z];
+  const int i = blockIdx.x * 256 + threadIdx.x, j0 = blockIdx.y * 256;
+  if ((int)blockIdx.x * 256 >= n || j0 >= n) return;
+  el += (int64_t)blockIdx.z * stride;
+  if (j0 + (int)threadIdx.x < n) s[threadIdx.x] = el[j0 + threadIdx.x];
+  __syncthreads();
+  if (i >= n) return;
+  const SortEl x = el[i];
+  const int jn = min(256, n - j0);
+  unsigned int c = 0;
+#pragma unroll 4
+  for (int t = 0; t < jn; ++t) c += el_less(s[t], x) ? 1u : 0u;
+  atomicAdd(&place[(int64_t)blockIdx.z * pstride + i], c);
+}
+
+__global__ __launch_bounds__(256) void k_rank_place(const SortEl* __restrict__ el, SortEl* __restrict__ out,
+                                                    int64_t stride, const unsigned int* __restrict__ n_b,
+                                                    const unsigned int* __restrict__ place, int64_t pstride) {
+  const int64_t b = blockIdx.y;
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < (int)n_b[b]) out[b * stride + place[b * pstride + i]] = el[b * stride + i];
 }
 
 // Sorted pattern (increasing linear index) in three launches: per-chunk
@@ -1282,7 +1320,7 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
   // sizes that the host reads back at the end come first.  One plan is a chain
   // of small launches: with seven clears, twiddles per axis and precision, two
   // more uploads and a synchronisation for each set of sizes a 512^2 plan took 454
-  // us, now 347 us, and 256 plans of 256^2 with their features 3.22, now 3.02 ms.
+  // us, then 347 us, and 256 plans of 256^2 with their features 3.22, now 3.02 ms.
   const size_t nhist = (size_t)cnt * (kHist1 + kHist2);
   size_t zat = 0;
   auto ztake = [&zat](size_t bytes) {
@@ -1383,27 +1421,39 @@ static mor_status plan_build_batch(mor_plan* const* P, const int cnt, const uint
     k_fill_u32<<<(cnt + 255) / 256, 256, 0, st>>>(ccount, cnt, (unsigned int)nmain);
     MOR_LAUNCH_CHECK("fill_counts");
   }
-  k_fill_sentinel<<<dim3((unsigned)((seg + 255) / 256), nb), 256, 0, st>>>(keys, nsorted, seg, npow2);
-  MOR_LAUNCH_CHECK("fill_sentinel");
-  const int64_t nsort = (int64_t)cnt * seg;
-  const int tile = (int)std::min<int64_t>(seg, 2048);
-  const unsigned nt = (unsigned)std::max(1, tile / 2);
-  if (seg >= 2) {
-    const unsigned ntiles = (unsigned)(nsort / tile);
-    const unsigned npairb = (unsigned)((nsort / 2 + 255) / 256);
-    k_bitonic_local<<<ntiles, nt, tile * sizeof(SortEl), st>>>(keys, tile, seg, 0, npow2);
-    MOR_LAUNCH_CHECK("bitonic_local");
-    for (int64_t k = 2 * (int64_t)tile; k <= seg; k <<= 1) {
-      for (int64_t j = k >> 1; j >= tile; j >>= 1) {
-        k_bitonic_global<<<npairb, 256, 0, st>>>(keys, nsort, seg, k, j, npow2);
-        MOR_LAUNCH_CHECK("bitonic_global");
-      }
-      k_bitonic_local<<<ntiles, nt, tile * sizeof(SortEl), st>>>(keys, tile, seg, k, npow2);
-      MOR_LAUNCH_CHECK("bitonic_local");
-    }
-  }
   const int64_t nrank = seg + nselfc;  // per-plan stride of the rank order
   MOR_HIP_TRY(ranked.alloc(sc, (size_t)cnt * nrank));
+  const int64_t most = keys == cand.p ? maxc : nmain;
+  if (seg > 2048 && (double)cnt * (double)most * (double)most <= kRankPairs) {
+    unsigned int* place = (unsigned int*)ranked.p;  // (filled below, when the places are done with)
+    SortEl* to = keys == cand.p ? el.p : cand.p;
+    const unsigned blocks = (unsigned)((most + 255) / 256);
+    MOR_HIP_TRY(hipMemsetAsync(place, 0, (size_t)cnt * seg * sizeof(unsigned int), st));
+    k_rank_count<<<dim3(blocks, blocks, nb), 256, 0, st>>>(keys, npow2, nsorted, place, seg);
+    k_rank_place<<<dim3(blocks, nb), 256, 0, st>>>(keys, to, npow2, nsorted, place, seg);
+    MOR_LAUNCH_CHECK("rank");
+    keys = to;
+  } else {
+    k_fill_sentinel<<<dim3((unsigned)((seg + 255) / 256), nb), 256, 0, st>>>(keys, nsorted, seg, npow2);
+    MOR_LAUNCH_CHECK("fill_sentinel");
+    const int64_t nsort = (int64_t)cnt * seg;
+    const int tile = (int)std::min<int64_t>(seg, 2048);
+    const unsigned nt = (unsigned)std::max(1, tile / 2);
+    if (seg >= 2) {
+      const unsigned ntiles = (unsigned)(nsort / tile);
+      const unsigned npairb = (unsigned)((nsort / 2 + 255) / 256);
+      k_bitonic_local<<<ntiles, nt, tile * sizeof(SortEl), st>>>(keys, tile, seg, 0, npow2);
+      MOR_LAUNCH_CHECK("bitonic_local");
+      for (int64_t k = 2 * (int64_t)tile; k <= seg; k <<= 1) {
+        for (int64_t j = k >> 1; j >= tile; j >>= 1) {
+          k_bitonic_global<<<npairb, 256, 0, st>>>(keys, nsort, seg, k, j, npow2);
+          MOR_LAUNCH_CHECK("bitonic_global");
+        }
+        k_bitonic_local<<<ntiles, nt, tile * sizeof(SortEl), st>>>(keys, tile, seg, k, npow2);
+        MOR_LAUNCH_CHECK("bitonic_local");
+      }
+    }
+  }
   // 4. selection, and the slot tables of the warm-start network (no plan has
   // more slots than M; the device knows how many)
   k_merge_select<<<dim3((unsigned)((nrank + 255) / 256), nb), 256, 0, st>>>(
