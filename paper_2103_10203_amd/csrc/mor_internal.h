@@ -129,7 +129,7 @@ struct MatDev {
 
 // Per-RVE iteration state.
 struct RveState {
-  int32_t active;
+  int32_t active;   // the RVE iterates; written by column and decision launches, read by row launches
   int32_t iters;
   int32_t status;   // mor_status of the RVE
   int32_t plan;     // index into the plan table
@@ -137,7 +137,8 @@ struct RveState {
   double denom;     // N * ||eps_bar||_F (or N when eps_bar = 0)
   double tol;
   int32_t max_iter;
-  int32_t warm_ok;  // 1: the warm start (if any) is used; 0: it held a NaN/Inf and the RVE starts cold
+  int16_t warm_ok;  // 1: the warm start (if any) is used; 0: it held a NaN/Inf and the RVE starts cold
+  int16_t ended;    // the stop decision; written by the launch that takes it, read by later launches only
 };
 
 // Kernel ids of the profiling counters.

@@ -1105,6 +1105,7 @@ std::vector<RveState> fresh_states(const SolveCtx& cx, const std::vector<mor_pla
     r.tol = tol;
     r.max_iter = max_iter;
     r.warm_ok = 1;
+    r.ended = 0;
   }
   return hs;
 }

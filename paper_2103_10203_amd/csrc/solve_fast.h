@@ -188,8 +188,9 @@ __device__ __forceinline__ void row_tile(const PlanDev* __restrict__ plans, cons
   const int nlast = P.nlast;
   // Stop decision of the previous iteration, taken by the first wavefront of
   // every tile (same order of the sum, so same result, in each) and recorded
-  // by tile 0; tiles that start after that see active = 0 above, which is the
-  // same decision.  The loads are issued here and summed while the first
+  // by tile 0 in fields that no row launch reads, so that every wavefront of
+  // every tile passes the check of `active` above alike, whenever it starts.
+  // The loads are issued here and summed while the first
   // gather is in flight: nothing is stored before the check.  It saves the
   // launch of k_converge (2.4-4.5 us of the 21-26 us an iteration of one
   // 256^2 or 512^2 RVE took).
@@ -534,7 +535,10 @@ __device__ __forceinline__ void col_tile(const PlanDev* __restrict__ plans, cons
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   __shared__ int coff[CB + 1];
   __shared__ double cwt[CB];  // Parseval weight of each column of the block (1 or 2)
-  if (MODE == MODE_ITER && !st[b].active) return;
+  if (MODE == MODE_ITER && st[b].ended) {
+    if (tile == 0 && tid == 0) st[b].active = 0;  // no column workgroup reads it
+    return;
+  }
   const PlanDev& P = plans[st[b].plan];
   const int ncol = P.ncol;
   const int j0 = tile * CB;
@@ -792,7 +796,7 @@ __global__ __launch_bounds__((mid_threads<N1>())) void k_mid_fast(
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int tid = threadIdx.x;
   const int b = rve_list[blockIdx.z];
-  if (check_active && !st[b].active) return;
+  if (check_active && st[b].ended) return;
   const PlanDev& P = plans[st[b].plan];
   const int j2 = blockIdx.y;
   if (j2 >= P.nlast) return;

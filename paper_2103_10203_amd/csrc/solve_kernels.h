@@ -406,7 +406,10 @@ __global__ __launch_bounds__(256) void k_col(const PlanDev* __restrict__ plans, 
                                              double* __restrict__ part, MT mat, int cb) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int b = rve_list[blockIdx.y];
-  if (MODE == MODE_ITER && !st[b].active) return;
+  if (MODE == MODE_ITER && st[b].ended) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) st[b].active = 0;  // no column workgroup reads it
+    return;
+  }
   const PlanDev& P = plans[st[b].plan];
   const int ncol = P.ncol;
   const int j0 = blockIdx.x * cb;
@@ -533,7 +536,7 @@ __global__ __launch_bounds__(256) void k_mid(const PlanDev* __restrict__ plans, 
                                              cpx<T>* __restrict__ Yc, Offs off, int xb, int check_active) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
   const int b = rve_list[blockIdx.z];
-  if (check_active && !st[b].active) return;
+  if (check_active && st[b].ended) return;
   const PlanDev& P = plans[st[b].plan];
   const int j2 = blockIdx.y;
   if (j2 >= P.nlast) return;
@@ -663,12 +666,16 @@ __device__ __forceinline__ int stop_rule(const RveState& S, double sum, double* 
   return -1;
 }
 
-// Ends an RVE (one thread per RVE).
+// Ends an RVE (one thread per RVE).  A row launch that takes the decision may
+// still be starting workgroups, and wavefronts of one workgroup, when this
+// stores: nothing that the same launch reads elsewhere may be stored here.  So
+// it marks `ended`, which the axis-1 and column launches check; the column
+// launch that finds it set clears `active`, which the row launches check.
 __device__ __forceinline__ void stop_rve(RveState& S, int status, double r, unsigned int* __restrict__ active_count) {
   if (status < 0) return;
   S.resid = r;
   S.status = status;
-  S.active = 0;
+  S.ended = 1;
   atomicSub(active_count, 1u);
 }
 
@@ -699,7 +706,10 @@ static __global__ __launch_bounds__(256) void k_converge(const PlanDev* __restri
   if (i >= nrve) return;  // uniform over the wavefront
   const int b = rve_list[i];
   RveState& S = st[b];
-  if (!S.active) return;
+  if (S.ended) {
+    if (lane == 0) S.active = 0;
+    return;
+  }
   const double* p = dec.part + off.part[b];
   const int n = (plans[S.plan].ncol + dec.cb - 1) / dec.cb;
   const double sum = part_sum(p, n, lane, lane < n ? p[lane] : 0.0, lane + 64 < n ? p[lane + 64] : 0.0);
@@ -707,6 +717,7 @@ static __global__ __launch_bounds__(256) void k_converge(const PlanDev* __restri
   double r = 0.0;
   const int end = stop_rule(S, sum, &r);
   stop_rve(S, end, r, dec.active);
+  if (end >= 0) S.active = 0;
   if (end < 0 && dec.chunk) {
     const double t = S.tol * S.denom;
     const float m = 0.5f * log2f((float)(sum / (t * t)));  // at least 0: r >= tol
