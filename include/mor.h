@@ -457,9 +457,11 @@ mor_status mor_warm_apply(const mor_plan_t* plans, int64_t nplans, const int64_t
  * and 384-point last axes (variant 2), whose radix-4 register passes leave
  * room for the plastic state; mor_tune_get reports a selection, or 0 when
  * there is none.  At its default variant a row length with few
- * workgroups in the call runs a kernel with one component per wavefront
- * instead, equal to the variants up to FP32 rounding.  The selection is per process, shared by
- * all threads and devices.
+ * workgroups in the call runs a kernel that gives every strain component its
+ * own threads instead, with the default variant's bits; a selected variant other
+ * than the default runs in calls of every size, so tune on calls of the size
+ * that is to be fast.  The selection is per process, shared by all threads and
+ * devices.
  *   kernel  MOR_KERNEL_ROW (last axis) or MOR_KERNEL_COL (axis 0)
  *   ndim    2 or 3; length = the grid's last-axis length n[ndim-1] (row) or
  *           its axis-0 length n[0] (column)

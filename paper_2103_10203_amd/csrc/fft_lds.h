@@ -35,6 +35,29 @@ __device__ __forceinline__ cpx<T> mul_si(cpx<T> a) {
   return SIGN > 0 ? cpx<T>{-a.y, a.x} : cpx<T>{a.y, -a.x};
 }
 
+// Arithmetic with its roundings spelled out.  Of two products that meet in a sum
+// the compiler fuses one, chosen by how often each is used and by its place in
+// the block, so the same source rounds differently in two kernels.  The row
+// kernels that stand in for each other by the size of a call must not: an RVE
+// gives the same bits alone and in a batch.  mul_rn is a product that is rounded
+// by itself, mad a product that is fused with its sum (as a contraction, not a
+// call of fma: that the scheduler places worse, 182 registers instead of 166
+// for a row of 512).  c of mad is a sum, a value or a mul_rn.
+template <typename T>
+__device__ __forceinline__ T mul_rn(T a, T b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+template <typename T>
+__device__ __forceinline__ T mad(T a, T b, T c) {
+#pragma clang fp contract(fast)
+  return a * b + c;
+}
+template <typename T>
+__device__ __forceinline__ cpx<T> cmul_mad(cpx<T> a, cpx<T> b) {
+  return {mad(a.x, b.x, -mul_rn(a.y, b.y)), mad(a.x, b.y, mul_rn(a.y, b.x))};
+}
+
 struct FftDesc {
   int32_t n;
   int32_t nst;

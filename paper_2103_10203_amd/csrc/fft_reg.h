@@ -41,7 +41,7 @@ __device__ __forceinline__ cpx<T> rot16(cpx<T> a) {
   else {
     constexpr T c = (T)c16(K);
     constexpr T s = (T)(SIGN * s16(K));
-    return {a.x * c - a.y * s, a.x * s + a.y * c};
+    return cmul_mad(a, cpx<T>{c, s});
   }
 }
 
@@ -65,11 +65,11 @@ struct Dft<3, SIGN> {
     const T h = (T)0.86602540378443864676;
     cpx<T> u0 = v[0], u1 = v[1], u2 = v[2];
     cpx<T> sm = cadd(u1, u2);
-    cpx<T> df = cscale(mul_i<SIGN>(csub(u1, u2)), h);
-    cpx<T> base = {u0.x - T(0.5) * sm.x, u0.y - T(0.5) * sm.y};
+    const cpx<T> d = mul_i<SIGN>(csub(u1, u2));
+    const cpx<T> base = {mad(T(-0.5), sm.x, u0.x), mad(T(-0.5), sm.y, u0.y)};
     v[0] = cadd(u0, sm);
-    v[1] = cadd(base, df);
-    v[2] = csub(base, df);
+    v[1] = {mad(d.x, h, base.x), mad(d.y, h, base.y)};
+    v[2] = {mad(d.x, -h, base.x), mad(d.y, -h, base.y)};
   }
 };
 
@@ -97,8 +97,9 @@ struct Dft<6, SIGN> {
     Dft<3, SIGN>::run(o);
     const T h = (T)0.86602540378443864676;
     // w6^1 = 1/2 + SIGN i h, w6^2 = -1/2 + SIGN i h
-    const cpx<T> o1 = {T(0.5) * o[1].x - SIGN * h * o[1].y, T(0.5) * o[1].y + SIGN * h * o[1].x};
-    const cpx<T> o2 = {T(-0.5) * o[2].x - SIGN * h * o[2].y, T(-0.5) * o[2].y + SIGN * h * o[2].x};
+    const T hs = SIGN > 0 ? h : -h;
+    const cpx<T> o1 = {mad(T(0.5), o[1].x, -mul_rn(hs, o[1].y)), mad(T(0.5), o[1].y, mul_rn(hs, o[1].x))};
+    const cpx<T> o2 = {mad(T(-0.5), o[2].x, -mul_rn(hs, o[2].y)), mad(T(-0.5), o[2].y, mul_rn(hs, o[2].x))};
     v[0] = cadd(e[0], o[0]);
     v[3] = csub(e[0], o[0]);
     v[1] = cadd(e[1], o1);
@@ -144,10 +145,10 @@ struct Dft<9, SIGN> {
       for (int n1 = 0; n1 < 3; ++n1) a[n2][n1] = v[3 * n1 + n2];
       Dft<3, SIGN>::run(a[n2]);
     }
-    a[1][1] = cmul(a[1][1], {c1, s1});
-    a[1][2] = cmul(a[1][2], {c2, s2});
-    a[2][1] = cmul(a[2][1], {c2, s2});
-    a[2][2] = cmul(a[2][2], {c4, s4});
+    a[1][1] = cmul_mad(a[1][1], {c1, s1});
+    a[1][2] = cmul_mad(a[1][2], {c2, s2});
+    a[2][1] = cmul_mad(a[2][1], {c2, s2});
+    a[2][2] = cmul_mad(a[2][2], {c4, s4});
 #pragma unroll
     for (int k1 = 0; k1 < 3; ++k1) {
       cpx<T> b[3] = {a[0][k1], a[1][k1], a[2][k1]};
@@ -250,7 +251,7 @@ __device__ __forceinline__ void pass_twiddle(cpx<T>* v, int k, const cpx<T>* tw)
   if constexpr (P > 1) {
     constexpr int ST = N / (P * R);
 #pragma unroll
-    for (int j = 1; j < R; ++j) v[j] = cmul(v[j], twid<SIGN, TWS>(tw, j * k * ST));
+    for (int j = 1; j < R; ++j) v[j] = cmul_mad(v[j], twid<SIGN, TWS>(tw, j * k * ST));
   }
 }
 

@@ -1148,9 +1148,9 @@ void choose_row(const SolveCtx& cx, Group& g) {
   const int rows = g.ndim == 2 ? g.n0 : g.n0 * g.n1;
   g.rb_iter = g.rb;
   // lengths of row_fast: the component-parallel kernel has the factors of the
-  // default variant and stands in for that one only.  Its results differ from
-  // row_fast's by rounding (in registers the compiler merges products of the
-  // law and the transforms that here meet through LDS).
+  // default variant and stands in for that one only, with the same bits (the
+  // operations and their roundings are the same), so that an RVE's result does
+  // not depend on how many others share the call.
   const int nh = nlen / 2;
   if (!g.fast_row || cx.dft || g.rvar != row_default(cx.C, nh, cx.j2)) return;
   if ((int64_t)cx.C * g.nlast_max * rows * (int64_t)sizeof(cpx<float>) >= (1LL << 31)) return;

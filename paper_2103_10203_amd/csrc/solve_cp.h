@@ -165,7 +165,7 @@ __global__ __launch_bounds__(whole_waves(C * RB * (NH / RowF<C, NH, MAT>::RL))) 
         const int r = t % RB, k = (t / RB) % KH, c = t / (RB * KH);
         cpx<T>* x = buf + (c * RB + r) * SS;
         const cpx<T> a = cadd(xa[u], cconj(xb[u]));
-        const cpx<T> d = cmul(csub(xa[u], cconj(xb[u])), cconj(tw[pad16(k)]));
+        const cpx<T> d = cmul_mad(csub(xa[u], cconj(xb[u])), cconj(tw[pad16(k)]));
         x[pad16(k)] = {a.x - d.y, a.y + d.x};
         if (k != 0 && 2 * k != NH) x[pad16(NH - k)] = {a.x + d.y, d.x - a.y};
       }
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(whole_waves(C * RB * (NH / RowF<C, NH, MAT>::RL))) 
 #pragma unroll
     for (int j = 0; j < RL; ++j) v[j] = seq[pad16(i + j * TR)];
 #pragma unroll
-    for (int j = 1; j < RL; ++j) v[j] = cmul(v[j], rtw[j]);
+    for (int j = 1; j < RL; ++j) v[j] = cmul_mad(v[j], rtw[j]);
     Dft<RL, +1>::run(v);
 #pragma unroll
     for (int j = 0; j < RL; ++j) seq[pad16(i + j * TR)] = v[j];
@@ -287,7 +287,7 @@ __global__ __launch_bounds__(whole_waves(C * RB * (NH / RowF<C, NH, MAT>::RL))) 
     Dft<RL, -1>::run(v);
     if constexpr (kPreTwiddle) {
 #pragma unroll
-      for (int j = 1; j < RL; ++j) v[j] = cmul(v[j], cconj(rtw[j]));
+      for (int j = 1; j < RL; ++j) v[j] = cmul_mad(v[j], cconj(rtw[j]));
     }
   }
   __syncthreads();
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(whole_waves(C * RB * (NH / RowF<C, NH, MAT>::RL))) 
     const cpx<T> Zk = z[pad16(k == NH ? 0 : k)];
     const cpx<T> Zc = cconj(z[pad16(k == 0 ? 0 : NH - k)]);
     const cpx<T> sm = cadd(Zk, Zc);
-    const cpx<T> wd = cmul(tw[pad16(k)], csub(Zk, Zc));
+    const cpx<T> wd = cmul_mad(tw[pad16(k)], csub(Zk, Zc));
     buf_store<T>(rs, (uint32_t)c * cbytes + (uint32_t)j * (uint32_t)rows * ES + (uint32_t)(r0 + r) * ES,
                  {T(0.5) * (sm.x + wd.y), T(0.5) * (sm.y - wd.x)});
   }

@@ -276,7 +276,7 @@ __device__ __forceinline__ void row_tile(const PlanDev* __restrict__ plans, cons
         cpx<float>* x = buf + rg * SS;
         const cpx<float> Xk = xa[u], Xm = xb[u];
         const cpx<float> a = cadd(Xk, cconj(Xm));
-        const cpx<float> d = cmul(csub(Xk, cconj(Xm)), cconj(T[pad16(k)]));
+        const cpx<float> d = cmul_mad(csub(Xk, cconj(Xm)), cconj(T[pad16(k)]));
         x[fftr::padp<PS>(k)] = {a.x - d.y, a.y + d.x};
         if (k != 0 && 2 * k != NH) x[fftr::padp<PS>(NH - k)] = {a.x + d.y, d.x - a.y};
       }
@@ -291,7 +291,7 @@ __device__ __forceinline__ void row_tile(const PlanDev* __restrict__ plans, cons
 #pragma unroll
       for (int j = 0; j < RL; ++j) v[c][j] = src[fftr::padp<PS>(i + j * TR)];
 #pragma unroll
-      for (int j = 1; j < RL; ++j) v[c][j] = cmul(v[c][j], rtw[j]);
+      for (int j = 1; j < RL; ++j) v[c][j] = cmul_mad(v[c][j], rtw[j]);
       Dft<RL, +1>::run(v[c]);
     }
     __syncthreads();
@@ -393,7 +393,7 @@ __device__ __forceinline__ void row_tile(const PlanDev* __restrict__ plans, cons
     constexpr bool kPreTwiddle = R2 * RL == NH;
     if constexpr (kPreTwiddle) {
 #pragma unroll
-      for (int j = 1; j < RL; ++j) v[c][j] = cmul(v[c][j], cconj(rtw[j]));
+      for (int j = 1; j < RL; ++j) v[c][j] = cmul_mad(v[c][j], cconj(rtw[j]));
     }
     {
       cpx<float>* dst = buf + r * SS;
@@ -417,7 +417,7 @@ __device__ __forceinline__ void row_tile(const PlanDev* __restrict__ plans, cons
         const cpx<float> Zk = z[fftr::padp<PS>(k == NH ? 0 : k)];
         const cpx<float> Zc = cconj(z[fftr::padp<PS>(k == 0 ? 0 : NH - k)]);
         const cpx<float> sm = cadd(Zk, Zc);
-        const cpx<float> wd = cmul(T[pad16(k)], csub(Zk, Zc));
+        const cpx<float> wd = cmul_mad(T[pad16(k)], csub(Zk, Zc));
         store_c(rs, (uint32_t)j * (uint32_t)rows * 8u + rowb, {0.5f * (sm.x + wd.y), 0.5f * (sm.y - wd.x)});
       }
     }

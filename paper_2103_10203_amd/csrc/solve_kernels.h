@@ -42,7 +42,8 @@ struct Comp<6> {
 };
 
 // Pointwise polarisation tau = sigma(eps) - C0:eps (step a) and, if wanted,
-// sigma itself and the updated J2 state.
+// sigma itself and the updated J2 state.  Roundings are spelled out (mul_rn,
+// mad): every row kernel that computes it gets the same bits.
 template <int C, int MAT>
 __device__ __forceinline__ void constitutive(const float* e, int ph, const MatDev& m, const float* stin, float* tau,
                                              float* sig, float* stout) {
@@ -57,11 +58,11 @@ __device__ __forceinline__ void constitutive(const float* e, int ph, const MatDe
     const float lam = p1 ? m.lam[1] : m.lam[0], mu = p1 ? m.mu[1] : m.mu[0];
     const float dl = p1 ? m.dl[1] : m.dl[0], dm = p1 ? m.dm[1] : m.dm[0];
 #pragma unroll
-    for (int i = 0; i < C; ++i) tau[i] = (i < ND ? dl * tr : 0.f) + dm * e[i];
+    for (int i = 0; i < C; ++i) tau[i] = i < ND ? mad(dm, e[i], mul_rn(dl, tr)) : mul_rn(dm, e[i]);
     if (sig) {
 #pragma unroll
-      for (int i = 0; i < C; ++i) sig[i] = (i < ND ? lam * tr : 0.f) + 2.f * mu * e[i];
-      if (C == 3) sig[3] = lam * tr;
+      for (int i = 0; i < C; ++i) sig[i] = i < ND ? mad(2.f * mu, e[i], mul_rn(lam, tr)) : mul_rn(2.f * mu, e[i]);
+      if (C == 3) sig[3] = mul_rn(lam, tr);
     }
   } else {
     // full 3D tensors, order 11,22,33,23,13,12
@@ -83,44 +84,46 @@ __device__ __forceinline__ void constitutive(const float* e, int ph, const MatDe
     float st[6], s[6];
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
-      st[i] = (i < 3 ? lam * tre : 0.f) + 2.f * mu * ee[i];
-      s[i] = 2.f * mu * (i < 3 ? ee[i] - tre * (1.f / 3.f) : ee[i]);
+      st[i] = i < 3 ? mad(2.f * mu, ee[i], mul_rn(lam, tre)) : mul_rn(2.f * mu, ee[i]);
+      s[i] = mul_rn(2.f * mu, i < 3 ? mad(tre, -(1.f / 3.f), ee[i]) : ee[i]);
     }
-    const float ns = sqrtf(s[0] * s[0] + s[1] * s[1] + s[2] * s[2] + 2.f * (s[3] * s[3] + s[4] * s[4] + s[5] * s[5]));
-    const float q = 1.22474487139158905f * ns;
+    const float diag = mad(s[2], s[2], mad(s[1], s[1], mul_rn(s[0], s[0])));
+    const float shear = mad(s[5], s[5], mad(s[4], s[4], mul_rn(s[3], s[3])));
+    const float ns = sqrtf(mad(2.f, shear, diag));
     const float H = p1 ? m.H[1] : m.H[0];
-    const float f = q - ((p1 ? m.sy[1] : m.sy[0]) + H * alpha);
+    const float f = mad(1.22474487139158905f, ns, -mad(H, alpha, p1 ? m.sy[1] : m.sy[0]));
     float sg[6];
     float dg = 0.f, fac = 0.f;
     if ((p1 ? m.plastic[1] : m.plastic[0]) && f > 0.f) {
-      dg = f / (3.f * mu + H);
-      fac = 1.22474487139158905f * dg / ns;
+      dg = f / mad(3.f, mu, H);
+      fac = mul_rn(1.22474487139158905f, dg) / ns;
     }
 #pragma unroll
-    for (int i = 0; i < 6; ++i) sg[i] = st[i] - 2.f * mu * fac * s[i];
+    for (int i = 0; i < 6; ++i) sg[i] = mad(-mul_rn(2.f * mu, fac), s[i], st[i]);
     const float tr3 = E[0] + E[1] + E[2];
     if (C == 3) {
-      tau[0] = sg[0] - (m.lam0 * tr3 + 2.f * m.mu0 * E[0]);
-      tau[1] = sg[1] - (m.lam0 * tr3 + 2.f * m.mu0 * E[1]);
-      tau[2] = sg[5] - 2.f * m.mu0 * E[5];
+      tau[0] = sg[0] - mad(2.f * m.mu0, E[0], mul_rn(m.lam0, tr3));
+      tau[1] = sg[1] - mad(2.f * m.mu0, E[1], mul_rn(m.lam0, tr3));
+      tau[2] = mad(-2.f * m.mu0, E[5], sg[5]);
       if (sig) { sig[0] = sg[0]; sig[1] = sg[1]; sig[2] = sg[5]; sig[3] = sg[2]; }
       if (stout) {
-        stout[0] = EP[0] + fac * s[0];
-        stout[1] = EP[1] + fac * s[1];
-        stout[2] = EP[5] + fac * s[5];
-        stout[3] = EP[2] + fac * s[2];
+        stout[0] = mad(fac, s[0], EP[0]);
+        stout[1] = mad(fac, s[1], EP[1]);
+        stout[2] = mad(fac, s[5], EP[5]);
+        stout[3] = mad(fac, s[2], EP[2]);
         stout[4] = alpha + dg;
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < 6; ++i) tau[i] = sg[i] - ((i < 3 ? m.lam0 * tr3 : 0.f) + 2.f * m.mu0 * E[i]);
+      for (int i = 0; i < 6; ++i)
+        tau[i] = i < 3 ? sg[i] - mad(2.f * m.mu0, E[i], mul_rn(m.lam0, tr3)) : mad(-2.f * m.mu0, E[i], sg[i]);
       if (sig) {
 #pragma unroll
         for (int i = 0; i < 6; ++i) sig[i] = sg[i];
       }
       if (stout) {
 #pragma unroll
-        for (int i = 0; i < 6; ++i) stout[i] = EP[i] + fac * s[i];
+        for (int i = 0; i < 6; ++i) stout[i] = mad(fac, s[i], EP[i]);
         stout[6] = alpha + dg;
       }
     }
