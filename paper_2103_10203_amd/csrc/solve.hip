@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "dft_kernels.h"
+#include "schedule.h"
 #include "solve_cp.h"
 
 using namespace mor_k;
@@ -937,16 +938,6 @@ mor_status launch_row64(SolveCtx& cx, Group& g, dim3 gr, size_t shm, float* eps,
 // path (64) 27.3 / 29.2 ms, 128 RVEs of 256^2 (2048) 2.01 / 2.04 ms, 256 RVEs
 // (4096) 3.26 / 3.25 ms, eight of 128^3 (8192) 9.15 / 9.02 ms.
 constexpr int64_t kRowDecidesMax = 2048;
-// Most workgroups (of four rows) for which the iteration rows of a row_fast
-// length run on the component-parallel kernel instead.  It has a third of the
-// chain per wavefront and four times the workgroups, but more LDS traffic per
-// row, so it wins while the device has room: row_fast / component-parallel per
-// solve, 256^2 with 1, 4, 8, 16 RVEs (64, 256, 512, 1024 workgroups) 753 / 637,
-// 770 / 682, 801 / 785, 888 / 969 us; 384^2 with 1, 4 (96, 384) 889 / 699,
-// 960 / 887; J2 paths of 512^2 with 1, 4 (128, 512) 9.3 / 7.9, 13.6 / 13.0 ms, of
-// 128^2 with 16 (512) 7.3 / 5.8 ms; 64^2 with 16, 64, 256 (256, 1024, 4096)
-// 484 / 421, 498 / 464, 587 / 704 us.
-constexpr int64_t kCpFewMax = 512;
 bool row_decides(const SolveCtx& cx, const Group& g, int rows) {
   return (g.cp_row || g.fast_row) && !cx.persist && !cx.dft &&
          (int64_t)((rows + g.rb_iter - 1) / g.rb_iter) * (int64_t)g.rves.size() <= kRowDecidesMax;
@@ -1147,15 +1138,12 @@ void choose_row(const SolveCtx& cx, Group& g) {
   const int nlen = g.ndim == 2 ? g.n1 : g.n2;
   const int rows = g.ndim == 2 ? g.n0 : g.n0 * g.n1;
   g.rb_iter = g.rb;
-  // lengths of row_fast: the component-parallel kernel has the factors of the
-  // default variant and stands in for that one only, with the same bits (the
-  // operations and their roundings are the same), so that an RVE's result does
-  // not depend on how many others share the call.
   const int nh = nlen / 2;
-  if (!g.fast_row || cx.dft || g.rvar != row_default(cx.C, nh, cx.j2)) return;
-  if ((int64_t)cx.C * g.nlast_max * rows * (int64_t)sizeof(cpx<float>) >= (1LL << 31)) return;
-  const int rb = cp_row_rb(cx.C, nh, false, cx.j2);
-  if (rb == 0 || (int64_t)((rows + rb - 1) / rb) * (int64_t)g.rves.size() > kCpFewMax) return;
+  const int rb = g.fast_row ? cp_row_rb(cx.C, nh, false, cx.j2) : 0;
+  const int64_t lines = (int64_t)cx.C * g.nlast_max * rows * (int64_t)sizeof(cpx<float>);
+  if (!mor_sched::rows_by_component({g.fast_row, g.rvar == row_default(cx.C, nh, cx.j2), cx.dft, cx.persist, lines, rb,
+                                     rows, (int64_t)g.rves.size()}))
+    return;
   g.cp_few = true;
   g.rb_iter = rb;
 }
