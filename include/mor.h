@@ -476,9 +476,14 @@ mor_status mor_tune_set(int32_t kernel, int32_t ndim, int32_t length, int32_t va
  * fewest runs of about equal size whose transform lines fit `bytes`, but
  * into no runs of fewer than `min_rves` RVEs, and the iteration loop runs
  * each run's chunk of iterations before the next, so the lines stay in the
- * last-level cache between the row and column passes.  Large enough runs
- * are halved and iterate two at a time, on the solve's stream and one of the
- * library's (joined to it before the call returns), within the same bytes.
+ * last-level cache between the row and column passes.  Where each half keeps
+ * enough work, runs of half the bytes iterate two at a time instead, on the
+ * solve's stream and one of the library's (joined to it before the call
+ * returns), within the same bytes together.  A min_rves other than the default
+ * bounds those too; at the default they may be smaller (at least 1024 row
+ * workgroups and 6 MiB of lines each: eight RVEs of 128^3 go as four runs).
+ * Different grids of one call whose lines all fit 256 MB, or `bytes` if that is
+ * set lower than its default, iterate side by side on up to four streams.
  * Results do not depend on the cut (every RVE iterates on its own).  Defaults: 192 MiB
  * (MOR_SUBBATCH_MIB in the environment, in MiB, sets the start value) and
  * 128 RVEs; bytes = 0 keeps each grid's RVEs together; -1 keeps a value.

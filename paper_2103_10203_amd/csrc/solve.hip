@@ -172,7 +172,8 @@ struct Group {
   int rb_iter = 1;       // rows per workgroup of the iteration's row kernel
   bool cp_col = false;   // columns of the lengths outside ColCfg (and FP64)
   int* d_list = nullptr;
-  int lane = 0;          // stream its chunks run on (0: the solve's own)
+  int lane = 0;          // stream its chunks run on (0: the solve's own; -1: that, and alone on the device)
+  bool pair = false;     // one of the runs that go two at a time
 };
 
 // Size-specialised kernels available for (C, half row length) and (C, n0).
@@ -1101,10 +1102,9 @@ std::vector<RveState> fresh_states(const SolveCtx& cx, const std::vector<mor_pla
   return hs;
 }
 
-// Working-set limit of one sub-batch (bytes of transform lines): MI355X's
-// 256 MB Infinity Cache less room for the coefficients, tables and phase
-// maps the passes also stream.  MOR_SUBBATCH_MIB in the environment sets the
-// start value, mor_tune_subbatch changes it (0: one sub-batch per grid).
+// Working-set limit of one sub-batch (bytes of transform lines).
+// MOR_SUBBATCH_MIB in the environment sets the start value, mor_tune_subbatch
+// changes it (0: one sub-batch per grid).
 std::atomic<int64_t>& subbatch_limit() {
   static std::atomic<int64_t> v{[] {
     if (const char* e = getenv("MOR_SUBBATCH_MIB")) {
@@ -1112,16 +1112,13 @@ std::atomic<int64_t>& subbatch_limit() {
       const long long m = strtoll(e, &end, 10);
       if (end != e && m >= 0 && m < (1LL << 40)) return (int64_t)m << 20;
     }
-    return (int64_t)192 << 20;
+    return mor_sched::kRunBytes;
   }()};
   return v;
 }
-size_t subbatch_bytes() { return (size_t)subbatch_limit().load(); }
-// Fewest RVEs of a sub-batch: below this the per-launch cost of the extra
-// launches outweighs the cache hits (3D RVEs of 128^3 lose 3 % when cut into
-// runs of two).
+// Fewest RVEs of a sub-batch.
 std::atomic<int64_t>& subbatch_min_rves() {
-  static std::atomic<int64_t> v{128};
+  static std::atomic<int64_t> v{mor_sched::kRunRves};
   return v;
 }
 
@@ -1147,28 +1144,6 @@ void choose_row(const SolveCtx& cx, Group& g) {
   g.cp_few = true;
   g.rb_iter = rb;
 }
-
-// Lanes: sub-batches have nothing to do with each other, so some run their
-// chunks on streams of their own, forked from and joined to the solve's stream
-// around every chunk.
-//  * Several grids: a grid whose launches do not fill the device leaves CUs
-//    idle, so grids run side by side, while the transform lines of all of them
-//    fit the 256 MB Infinity Cache (beyond that they drive each other out): in
-//    turn / side by side, 16 RVEs each of 96x144, 162x108, 288x192 (12 MB)
-//    1976 / 1168 us, of 128^2, 256^2, 384^2 64 each (80 MB) 4.36 / 3.32 ms, 512
-//    each (630 MB) 24.2 / 24.7 ms.
-//  * Otherwise two at a time, each within half the sub-batch limit, so that
-//    one's row pass (bound by VALU issue) overlaps the other's column pass
-//    (bound by latency), if each has at least kPairWgs row workgroups and
-//    kPairBytes of lines; one at a time / in pairs: 1024 RVEs of 256^2 13.1 / 12.2
-//    ms, 1536 of 128^2, 256^2, 384^2 23.7 / 22.3 ms, 16 of 128^3 17.8 / 16.2 ms,
-//    128 of 256^2 (1024 workgroups, 22 MB each) 1.95 / 1.76 ms, but 64 of them
-//    (512) 1.32 / 1.31, four of 48x72x96 (864) 1.69 / 1.76, and 512 of 64^2 (1024,
-//    but 5 MB each) 0.73 / 0.77 ms.
-constexpr int kLanes = 4;  // streams, the solve's own among them
-constexpr size_t kLanesBytes = (size_t)256 << 20;
-constexpr int64_t kPairWgs = 1024;
-constexpr size_t kPairBytes = (size_t)6 << 20;
 
 // Prepare the context: plan table, groups, offsets, states.
 mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::vector<int>& plan_of,
@@ -1291,7 +1266,7 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
   // pass writes are still cached when the column pass reads them and vice
   // versa (a batch of 1024 256^2 RVEs streams 350 MB of lines per pass).
   {
-    const size_t limit = subbatch_bytes();
+    const int64_t limit = subbatch_limit().load(), min_rves = subbatch_min_rves().load();
     const size_t es = cx.fp64 ? sizeof(cpx<double>) : sizeof(cpx<float>);
     auto line_bytes = [&](int b) {
       const mor_plan* p = plans[plan_of[b]];
@@ -1301,11 +1276,10 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
     };
     size_t all = 0;
     for (int64_t b = 0; b < B; ++b) all += line_bytes((int)b);
-    // grids side by side while all lines fit the cache, else (and for one
-    // grid) pairs of sub-batches side by side
+    // streams of its own for a run: not where the call may allocate none, records
+    // a graph or times its kernels
     const bool lanes = !cx.noalloc && !g_prof_on && !(opts && opts->use_graph);
-    const bool side = lanes && cx.groups.size() > 1 && all <= kLanesBytes;
-    const bool pairs = lanes && !side && limit > 0;
+    const bool side = lanes && mor_sched::grids_side_by_side((int64_t)cx.groups.size(), (int64_t)all, limit);
     std::vector<Group> split;
     for (const Group& g : cx.groups) {
       std::vector<size_t> yb(g.rves.size());
@@ -1314,25 +1288,19 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
         yb[q] = line_bytes(g.rves[q]);
         total += yb[q];
       }
-      // as few sub-batches as the limit allows, of about equal size (cut
-      // where the running sum passes the next multiple of total / parts)
-      const size_t minr = (size_t)std::max<int64_t>(1, subbatch_min_rves().load());
-      size_t parts = limit > 0 ? std::max<size_t>(1, std::min((total + limit - 1) / limit, g.rves.size() / minr)) : 1;
-      if (pairs) {
-        // two at a time: each within half the limit, an even number of them,
-        // unless that leaves too few row workgroups to one
-        const int rows = g.ndim == 2 ? g.n0 : g.n0 * g.n1;
-        const int64_t wgs = (int64_t)((rows + g.rb_iter - 1) / g.rb_iter) * (int64_t)g.rves.size();
-        const size_t want = std::max<size_t>((2 * total + limit - 1) / limit, 1);
-        const size_t p2 = std::min({(want + 1) / 2 * 2, (size_t)(wgs / kPairWgs) / 2 * 2, total / kPairBytes / 2 * 2,
-                                    g.rves.size() / 2 * 2});
-        if (p2 >= 2) parts = p2;
-      }
+      const int rows = g.ndim == 2 ? g.n0 : g.n0 * g.n1;
+      const int64_t wgs = (int64_t)((rows + g.rb_iter - 1) / g.rb_iter) * (int64_t)g.rves.size();
+      const mor_sched::Cut c =
+          mor_sched::cut_runs((int64_t)total, (int64_t)g.rves.size(), wgs, limit, min_rves, lanes && !side);
+      // of about equal size: cut where the running sum passes the next multiple
+      // of total / runs
       Group cur = g;
+      cur.pair = c.pairs;
       cur.rves.clear();
-      size_t run = 0, cut = 1;
+      size_t run = 0;
+      int64_t cut = 1;
       for (size_t q = 0; q < g.rves.size(); ++q) {
-        if (cut < parts && !cur.rves.empty() && (long double)run >= (long double)total * cut / parts) {
+        if (cut < c.runs && !cur.rves.empty() && (long double)run >= (long double)total * cut / c.runs) {
           split.push_back(cur);
           cur.rves.clear();
           ++cut;
@@ -1342,19 +1310,25 @@ mor_status setup(SolveCtx& cx, const std::vector<mor_plan*>& plans, const std::v
       }
       split.push_back(cur);
     }
-    if (pairs) {
-      // the sub-batches to the lane with fewer bytes so far, in order
+    if (side) {
+      // grid k, in order of appearance, on lane k mod kLanes
+      std::map<std::vector<int>, int> seen;
+      for (Group& g : split)
+        g.lane = seen.emplace(std::vector<int>{g.n0, g.n1, g.n2}, (int)seen.size()).first->second % mor_sched::kLanes;
+    } else if (lanes) {
+      // the runs that may share the device to the lane with fewer bytes so far, in
+      // order; the others go alone
       size_t sum[2] = {0, 0};
       for (Group& g : split) {
         size_t bytes = 0;
         for (int b : g.rves) bytes += line_bytes(b);
+        if (!g.pair && !mor_sched::shares_device((int64_t)bytes, limit)) {
+          g.lane = -1;
+          continue;
+        }
         g.lane = sum[1] < sum[0] ? 1 : 0;
         sum[g.lane] += bytes;
       }
-    } else if (side) {
-      // grid k, in order of appearance, on lane k mod kLanes
-      std::map<std::vector<int>, int> seen;
-      for (Group& g : split) g.lane = seen.emplace(std::vector<int>{g.n0, g.n1, g.n2}, (int)seen.size()).first->second % kLanes;
     }
     cx.groups.swap(split);
   }
@@ -1493,17 +1467,19 @@ struct GraphChunk {
   }
 };
 
-// The groups of each lane (Group::lane); one lane if there are no streams.
-std::vector<std::vector<Group*>> lanes_of(SolveCtx& cx) {
+// The groups of each lane (Group::lane), and those that go one after the other
+// on the solve's stream: all of them if there is one lane, or no streams.
+std::vector<std::vector<Group*>> lanes_of(SolveCtx& cx, std::vector<Group*>* alone) {
   std::vector<std::vector<Group*>> lanes(1);
   for (Group& g : cx.groups) {
+    if (g.lane < 0) continue;
     if (lanes.size() <= (size_t)g.lane) lanes.resize(g.lane + 1);
     lanes[g.lane].push_back(&g);
   }
-  if (lanes.size() > 1 && !cx.ws->side_streams(lanes.size() - 1)) {
-    lanes.assign(1, {});
-    for (Group& g : cx.groups) lanes[0].push_back(&g);
-  }
+  if (lanes.size() > 1 && !cx.ws->side_streams(lanes.size() - 1)) lanes.resize(1);
+  const bool one = lanes.size() == 1;
+  for (Group& g : cx.groups)
+    if (one || g.lane < 0) alone->push_back(&g);
   return lanes;
 }
 
@@ -1580,19 +1556,19 @@ mor_status run(SolveCtx& cx, const cpx<float>* warm, const mor_solve_opts* opts,
   // 15-25 us) and launches few iterations that find nothing to do (4-10 us
   // each).  When an RVE stops is decided on the device either way.
   const bool adapt = !gc.exec && !(opts && opts->check_every > 0);
-  const auto lanes = lanes_of(cx);
+  std::vector<Group*> alone;
+  const auto lanes = lanes_of(cx, &alone);
   int len = check;
   double prev = -1.0;  // margin log2(r / tol) at the last look
   for (unsigned int chunk = 1;; ++chunk) {
     cx.chunk_no = adapt && chunk <= kChunksCounted ? chunk : 0;
     if (gc.exec) {
       MOR_HIP_TRY(hipGraphLaunch(gc.exec, cx.st));
-    } else if (lanes.size() > 1) {
-      if ((s = chunk_of_lanes(cx, lanes, len)) != MOR_OK) return s;
     } else {
+      if (lanes.size() > 1 && (s = chunk_of_lanes(cx, lanes, len)) != MOR_OK) return s;
       // sub-batch outermost: its lines stay cached across its iterations
-      for (auto& g : cx.groups)
-        if ((s = do_chunk(cx, g, len)) != MOR_OK) return s;
+      for (Group* g : alone)
+        if ((s = do_chunk(cx, *g, len)) != MOR_OK) return s;
     }
     done += len;
     unsigned int* hact = cx.noalloc ? cx.h_active_local : cx.ws->h_active;

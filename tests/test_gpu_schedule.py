@@ -81,3 +81,28 @@ def test_persistent_equals_grid_j2(shape):
     assert np.array_equal(res[0][0].iterations, res[1][0].iterations)
     assert np.array_equal(res[0][0].eff_stress, res[1][0].eff_stress)
     assert bool((res[0][1] == res[1][1]).all())
+
+
+def test_pairs_beside_runs_that_go_alone():
+    """Under a limit of 24 MiB: 256 RVEs of 128^2 go as a pair of runs, 40 of 256^2
+    (too few workgroups for a pair, beyond half the limit) alone, and 20 of 64^2
+    beside the pair; with a set minimum of 129 RVEs nothing is paired.  The bits
+    are those of one run per grid."""
+    import paper_2103_10203_amd as mor
+    sizes = [128] * 256 + [256] * 40 + [64] * 20
+    plans = [mor.Plan(g, int(math.ceil(0.05 * g.size))) for g in (_map((n, n), 9) for n in (128, 256, 64))]
+    po = np.array([{128: 0, 256: 1, 64: 2}[n] for n in sizes])[np.random.default_rng(2).permutation(len(sizes))]
+    eb = synth.macro_strains(len(po), 3, 5e-3, seed=4)
+    keep = mor.tune_subbatch(0)
+    try:
+        want = mor.solve_multi(plans, po, eb, native_phases(), 1e-6, want_fields=True)
+        for limit, least in ((24 << 20, -1), (24 << 20, 129), (24 << 20, 64), (4 << 20, 1)):
+            mor.tune_subbatch(limit, least)
+            for _ in range(2):
+                got = mor.solve_multi(plans, po, eb, native_phases(), 1e-6, want_fields=True)
+                assert np.array_equal(got.iterations, want.iterations)
+                assert np.array_equal(got.residual, want.residual)
+                assert np.array_equal(got.eff_stress, want.eff_stress)
+                assert bool((got.strain == want.strain).all()) and bool((got.stress == want.stress).all())
+    finally:
+        mor.tune_subbatch(*keep)
