@@ -165,7 +165,10 @@ def cpu_baseline(gs, ebs, budget_s=12.0):
     return base, sig
 
 
-SOLVE_SOURCES = ("fft_lds.h", "fft_reg.h", "mor_internal.h", "solve_fast.h", "solve_kernels.h", "solve.hip")
+# every source that a solve's kernels and their launches are built from
+SOLVE_SOURCES = ("cp_col.hip", "cp_rb.h", "cp_row_2d.hip", "cp_row_3d.hip", "cp_row_f64.hip", "dft_kernels.h", "fft_lds.h",
+                 "fft_reg.h", "mor_internal.h", "schedule.h", "solve.hip", "solve_cp.h", "solve_fast.h",
+                 "solve_kernels.h")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "solve_256x256_m3277_b1024_hbm_traffic.txt")
 
 
@@ -220,7 +223,10 @@ def timed_batched(mor, plans, plan_of, ebs, ph, steps, warmup, warm_fn=None):
     The throughput is timed without per-kernel events (optionally with
     hipGraph replay of the iteration chunks); the per-kernel durations of the
     roofline come from a repetition of the same steps, launched eagerly with
-    HIP events around every kernel on the solve stream."""
+    HIP events around every kernel on the solve stream.  Profiled calls keep to
+    that one stream, so these are launches of whole runs (512 RVEs of the
+    headline batch), one at a time; the timed steps iterate smaller runs two
+    at a time."""
     import torch
 
     def step(**kw):
@@ -743,7 +749,8 @@ def main():
             "flops_note": "per RVE-iteration rows * C * 2 * 2.5 L log2 L + 25 N (FFT-path flops of the fused "
                           "row pass); peak = FP32 vector 157.3 TFLOP/s; frac_nonpacked against the 78.6 "
                           "TFLOP/s that FP32 FMAs reach without packed instructions (not generated here)",
-            "timing": "HIP events around every launch of the kernel in an eager repetition of the timed steps",
+            "timing": "HIP events around every launch of the kernel in an eager repetition of the timed steps on "
+                      "one stream (whole runs one at a time; the timed steps iterate runs in pairs on two streams)",
             "avg_launch_us": kr["ms"] * 1e3 / max(kr["launches"], 1), "launches": kr["launches"],
             "valu_issue_frac": measured_valu_issue("row"),
             "valu_note": "share of the 1024 SIMDs' VALU issue slots the kernel used (rocprofv3 SQ_INSTS_VALU, "
