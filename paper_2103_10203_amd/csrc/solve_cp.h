@@ -1,7 +1,12 @@
-// Component-parallel row kernel, and the column and axis-1 kernels of every
-// 2^a 3^b length of the usual ranges: compile-time transforms in FP32 and
-// FP64, launched through the plain functions at the end (each family is
-// compiled in a source file of its own).
+// Component-parallel row kernel, and the column kernels of the lengths that
+// solve_fast.h does not build: compile-time transforms in FP32 and FP64,
+// launched through the plain functions at the end (each family is compiled in a
+// source file of its own).  Built are, of the even 2^a 3^b lengths,
+//   2D rows and columns  32 to 512 but 486, FP32 and FP64 (FP32 columns of 24 too)
+//   3D rows              24 to 128, and 256, FP32
+//   3D axes 0 and 1      24 to 128, FP32 (axis 1 in solve_fast.h)
+// Every other length, and FP64 in 3D, runs the runtime-radix kernels of
+// solve_kernels.h at about a third of the speed.
 //
 // The row kernel of solve_fast.h keeps all strain components of a thread's
 // points in registers and transforms them one after the other: least LDS
